@@ -20,6 +20,7 @@ struct mm_sno {
     double scale = 1.0;
     uint16_t* w = nullptr;
     float2* tw = nullptr;  // nx x-twiddles then ny y-twiddles
+    float4* ex = nullptr;  // kept-mode table of the x transforms
     float* h = nullptr;    // two activation buffers
     float2* modes = nullptr;
     SnoArgs args;
@@ -37,7 +38,7 @@ uint16_t to_bf16(float f) {
 }
 
 void free_sno(mm_sno* s) {
-    void* p[] = {s->w, s->tw, s->h, s->modes};
+    void* p[] = {s->w, s->tw, s->ex, s->h, s->modes};
     for (void* q : p)
         if (q) (void)hipFree(q);
 }
@@ -87,9 +88,11 @@ int mm_sno_create(mm_sno** out, int32_t nx, int32_t ny, const float* weights, in
     if (e == hipSuccess) e = hipMalloc((void**)&s->tw, (size_t)(nx + ny) * sizeof(float2));
     if (e == hipSuccess) e = hipMalloc((void**)&s->h, 2 * SNO_C * n * sizeof(float));
     const size_t line = (size_t)SNO_C * ny * SNO_KX, kept = (size_t)SNO_C * SNO_KY * SNO_KX;
-    if (e == hipSuccess) e = hipMalloc((void**)&s->modes, (2 * line + 2 * kept) * sizeof(float2));
-    if (e == hipSuccess) e = configure_sno(ny);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->modes, (line + 2 * kept) * sizeof(float2));
+    if (e == hipSuccess) e = configure_sno(nx);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->ex, sno_ex_floats(nx) * sizeof(float));
     if (e == hipSuccess) e = sno_twiddles(s->tw, nx, s->stream);
+    if (e == hipSuccess) e = sno_ex(s->tw, nx, s->ex, s->stream);
     if (e == hipSuccess) e = sno_twiddles(s->tw + nx, ny, s->stream);
     int st = map_err(e);
     if (st == MM_OK) st = upload(s, weights, nweights);
@@ -120,14 +123,13 @@ int mm_sno_create(mm_sno** out, int32_t nx, int32_t ny, const float* weights, in
     a.proj = s->w + o;
     o += 3 * SNO_C;
     a.proj_b = s->w + o;
-    a.twx = s->tw;
+    a.ex = s->ex;
     a.twy = s->tw + nx;
     a.h0 = s->h;
     a.h1 = s->h + SNO_C * n;
-    a.H1 = s->modes;
-    a.G1 = s->modes + line;
-    a.Hh = s->modes + 2 * line;
-    a.Gh = s->modes + 2 * line + kept;
+    a.line = reinterpret_cast<float*>(s->modes);
+    a.Hh = s->modes + line;
+    a.Gh = s->modes + line + kept;
     *out = s;
     return MM_OK;
 }

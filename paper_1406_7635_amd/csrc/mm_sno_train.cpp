@@ -20,7 +20,8 @@ struct mm_sno_trainer {
     float* m1 = nullptr;
     float* m2 = nullptr;
     float2* tw = nullptr;   // nx then ny twiddles
-    float* act = nullptr;   // h[5], z[4], dh[2], dz, y
+    float4* ex = nullptr;   // kept-mode table of the x transforms
+    float* act = nullptr;   // h[5], GELU'[4], dz[2], y
     float2* modes = nullptr;
     float* part = nullptr;
     double* lpart = nullptr;
@@ -33,7 +34,7 @@ struct mm_sno_trainer {
 namespace {
 
 void free_tr(mm_sno_trainer* t) {
-    void* p[] = {t->w, t->tw, t->act, t->modes, t->part, t->lpart, t->scale, t->loss};
+    void* p[] = {t->w, t->tw, t->ex, t->act, t->modes, t->part, t->lpart, t->scale, t->loss};
     for (void* q : p)
         if (q) (void)hipFree(q);
 }
@@ -67,20 +68,21 @@ int mm_sno_train_create(mm_sno_trainer** out, int32_t nx, int32_t ny, int32_t ba
     const long long fld = (long long)batch * SNO_C * n;  // one activation array
     const long long kept = (long long)batch * SNO_C * SNO_KY * SNO_KX;
     const long long line = (long long)batch * SNO_C * ny * SNO_KX;
-    const int tiles = sno_train_tiles((long long)batch * n);
     const long long nw = SNO_NWEIGHTS;
     hipError_t e = hipMalloc((void**)&t->w, (size_t)(4 * nw) * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&t->tw, (size_t)(nx + ny) * sizeof(float2));
-    // h[0..4], z[0..3], dh[0..1], dz: 12 activation arrays, then y [B][3][n]
-    if (e == hipSuccess) e = hipMalloc((void**)&t->act, (size_t)(12 * fld + 3LL * batch * n) * sizeof(float));
+    // h[0..4], GELU'[0..3], dz[0..1]: 11 activation arrays, then y [B][3][n]
+    if (e == hipSuccess) e = hipMalloc((void**)&t->act, (size_t)(11 * fld + 3LL * batch * n) * sizeof(float));
     // H[0..3], modes, modes2: 6 kept-mode arrays, then the line array
     if (e == hipSuccess) e = hipMalloc((void**)&t->modes, (size_t)(6 * kept + line) * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&t->part, (size_t)tiles * (SNO_C * SNO_C + SNO_C) * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc((void**)&t->part, sno_train_part(nx, ny, batch) * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&t->lpart, (size_t)batch * 64 * 2 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&t->scale, (size_t)batch * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&t->loss, sizeof(double));
-    if (e == hipSuccess) e = configure_sno_train(ny);
+    if (e == hipSuccess) e = configure_sno_train(nx);
+    if (e == hipSuccess) e = hipMalloc((void**)&t->ex, sno_ex_floats(nx) * sizeof(float));
     if (e == hipSuccess) e = sno_twiddles(t->tw, nx, t->stream);
+    if (e == hipSuccess) e = sno_ex(t->tw, nx, t->ex, t->stream);
     if (e == hipSuccess) e = sno_twiddles(t->tw + nx, ny, t->stream);
     if (e == hipSuccess) {
         t->g = t->w + nw;
@@ -103,20 +105,19 @@ int mm_sno_train_create(mm_sno_trainer** out, int32_t nx, int32_t ny, int32_t ba
     a.batch = batch;
     a.w = t->w;
     a.g = t->g;
-    a.twx = t->tw;
+    a.ex = t->ex;
     a.twy = t->tw + nx;
     SnoTrainBufs& b = t->bufs;
     float* f = t->act;
     for (int l = 0; l <= SNO_LAYERS; ++l) b.h[l] = f + l * fld;
-    for (int l = 0; l < SNO_LAYERS; ++l) b.z[l] = f + (5 + l) * fld;
-    b.dh[0] = f + 9 * fld;
-    b.dh[1] = f + 10 * fld;
-    b.dz = f + 11 * fld;
-    b.y = f + 12 * fld;
+    for (int l = 0; l < SNO_LAYERS; ++l) b.gd[l] = f + (5 + l) * fld;
+    b.dz[0] = f + 9 * fld;
+    b.dz[1] = f + 10 * fld;
+    b.y = f + 11 * fld;
     for (int l = 0; l < SNO_LAYERS; ++l) b.H[l] = t->modes + l * kept;
     b.modes = t->modes + 4 * kept;
     b.modes2 = t->modes + 5 * kept;
-    b.line = t->modes + 6 * kept;
+    b.line = reinterpret_cast<float*>(t->modes + 6 * kept);
     b.part = t->part;
     b.lpart = t->lpart;
     b.scale = t->scale;

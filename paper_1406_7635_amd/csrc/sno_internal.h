@@ -27,14 +27,13 @@ struct SnoArgs {
     const uint16_t* pw_b[SNO_LAYERS];
     const uint16_t* proj;
     const uint16_t* proj_b;
-    const float2* twx;             // exp(-2 pi i m / nx), m < nx
+    const float4* ex;              // exp(-2 pi i kx x / nx) for the kept kx, [x][kx][re, im]
     const float2* twy;             // exp(-2 pi i m / ny), m < ny
     float* h0;                     // activations [32][ny][nx] (two buffers)
     float* h1;
-    float2* H1;                    // [32][ny][16] after the x transform
+    float* line;                   // [ny][32][16] complex after the x transform
     float2* Hh;                    // [32][16][16] kept modes
     float2* Gh;                    // [32][16][16] mixed modes
-    float2* G1;                    // [32][ny][16] after the inverse y transform
 };
 
 // offsets of the parameter groups in the flat weight array
@@ -55,39 +54,41 @@ struct SnoTrainArgs {
     int nx, ny, n, batch;
     const float* w;                // weights (flat, FP32)
     float* g;                      // gradient of the loss (flat)
-    const float2* twx;             // exp(-2 pi i m / nx)
+    const float4* ex;              // exp(-2 pi i kx x / nx) for the kept kx, [x][kx][re, im]
     const float2* twy;             // exp(-2 pi i m / ny)
 };
 struct SnoTrainBufs {
     float* h[SNO_LAYERS + 1];      // activations [B][32][n]: lift output, then each layer's output
-    float* z[SNO_LAYERS];          // pre-GELU values of each layer [B][32][n]
+    float* gd[SNO_LAYERS];         // GELU' of each layer [B][32][n]
     float2* H[SNO_LAYERS];         // kept modes of each layer's input [B][32][256]
-    float2* line;                  // [B][32][ny][16] (x transform / inverse y transform)
+    float* line;                   // [B][ny][32][16] complex after an x transform
     float2* modes;                 // [B][32][256]
     float2* modes2;                // [B][32][256]
     float* y;                      // prediction [B][3][n]
-    float* dh[2];                  // gradients with respect to activations [B][32][n]
-    float* dz;                     // [B][32][n]
-    float* part;                   // per-workgroup partial sums [tiles][1056]
+    float* dz[2];                  // gradients with respect to a layer's pre-GELU values [B][32][n]
+    float* part;                   // per-workgroup weight sums [sno_train_blocks][1155]
     double* lpart;                 // [B][64][2] loss partial sums
     float* scale;                  // [B] per-sample loss scale
     double* loss;                  // the batch loss
 };
-hipError_t configure_sno_train(int ny);
-int sno_train_tiles(long long pixels);
+hipError_t configure_sno_train(int nx);
+// floats of the weight-sum workspace
+size_t sno_train_part(int nx, int ny, int batch);
 hipError_t sno_train_grad(const SnoTrainArgs& a, const SnoTrainBufs& s, const float* m, const float* t,
                           hipStream_t st);
 hipError_t sno_train_adam(float* w, const float* g, float* m1, float* m2, long long n, float lr, float b1, float b2,
                           float eps, long long step, hipStream_t st);
 
 hipError_t sno_twiddles(float2* tw, int n, hipStream_t s);
+// the x transform's table from the twiddles of length nx; its size (x rounded up to 32)
+hipError_t sno_ex(const float2* twx, int nx, float4* ex, hipStream_t s);
+constexpr size_t sno_ex_floats(int nx) { return (size_t)((nx + 31) / 32) * 32 * 2 * SNO_KX; }
 // the forward pass of a created surrogate on a given stream, and its grid
 hipError_t sno_run(const mm_sno* s, const float* m, float* out, hipStream_t stream);
 void sno_grid(const mm_sno* s, int* nx, int* ny);
 // the whole forward pass: m [3][n] -> out [3][n]
 hipError_t sno_forward(const SnoArgs& a, const float* m, float* out, hipStream_t s);
-size_t sno_dftx_lds(int nx);
-// raise the LDS limit of the y transform (ny <= 512 rows: 69 KB)
-hipError_t configure_sno(int ny);
+// raise the LDS limit of the row passes (nx <= 512: 106 KB)
+hipError_t configure_sno(int nx);
 
 }  // namespace mm
