@@ -75,6 +75,12 @@ struct mm_ctx {
     // any grid, y of 2D grids whose column pass holds whole columns
     bool full_x = false, full_y = false;
     int win[3] = {1, 1, 1};  // tensor window per axis: n P, or n
+    // every buffer of mm_create lies in one allocation (a hipMalloc and a
+    // hipFree of each large one cost about 50 and 240 us); kbuf, ms, ms2 and spec
+    // are adjacent, `scratch_bytes` from kbuf on, and lend themselves as
+    // scratch of the kernel construction
+    void* arena = nullptr;
+    size_t scratch_bytes = 0;
     uint8_t* region = nullptr;
     double* params64 = nullptr;
     RegionLut* lut = nullptr;
@@ -139,9 +145,7 @@ hipError_t dalloc(mm_ctx* c, void** p, size_t bytes) {
 }
 
 void free_all(mm_ctx* c) {
-    void* ptrs[] = {c->region, c->params64, c->lut,      c->ptab,    c->tw,   c->spec,   c->khat, c->kbuf,
-                    c->ms,     c->ms2,      c->st,       c->partials, c->dft_tab, c->bsur, c->bexact, c->zker,
-                    c->sigma,  c->bth,      c->cub,      c->dmi};
+    void* ptrs[] = {c->arena, c->bsur, c->bexact, c->sigma, c->bth, c->cub, c->dmi};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete c->hparams;
@@ -819,26 +823,39 @@ int mm_create(mm_ctx** out, const mm_grid* g, const mm_params* p, const uint8_t*
     const long long maxblk_l = (c->ncell + NT - 1) / NT;
     const long long maxblk = maxblk_x > maxblk_l ? maxblk_x : maxblk_l;
 
-    int st = MM_OK;
-    auto A = [&](void** ptr, size_t bytes) {
-        if (st != MM_OK) return;
-        const hipError_t e = dalloc(c, ptr, bytes);
-        if (e != hipSuccess) st = map_err(e);
+    struct Slot {
+        void** p;
+        size_t bytes;
     };
-    A((void**)&c->region, (size_t)c->ncell);
-    A((void**)&c->params64, sizeof(mm_params));
-    A((void**)&c->lut, NREG * sizeof(RegionLut));
-    A((void**)&c->ptab, (size_t)NREG * NREG * sizeof(float));
-    A((void**)&c->tw, (size_t)c->pt * sizeof(cf));
-    A((void**)&c->spec, (size_t)c->spec_elems * sizeof(cf));
-    A((void**)&c->khat, (size_t)c->khat_elems * sizeof(float));
-    A((void**)&c->kbuf, (size_t)MAXK * 3 * c->ncell * sizeof(float));
-    A((void**)&c->ms, (size_t)3 * c->ncell * sizeof(float));
-    A((void**)&c->ms2, (size_t)3 * c->ncell * sizeof(float));
-    A((void**)&c->dft_tab, (size_t)2 * DFT_TABLE_BYTES);
-    if (c->yz) A((void**)&c->zker, (size_t)c->kx * (c->py / 2 + 1) * zkernel_floats(c->pz) * sizeof(float));
-    A((void**)&c->st, sizeof(DevState));
-    A((void**)&c->partials, (size_t)maxblk * 4 * sizeof(double));
+    const size_t fld = (size_t)3 * c->ncell * sizeof(float);
+    const Slot slots[] = {
+        {(void**)&c->kbuf, MAXK * fld},  // kbuf ... spec: the scratch range
+        {(void**)&c->ms, fld},
+        {(void**)&c->ms2, fld},
+        {(void**)&c->spec, (size_t)c->spec_elems * sizeof(cf)},
+        {(void**)&c->khat, (size_t)c->khat_elems * sizeof(float)},
+        {(void**)&c->zker, c->yz ? (size_t)c->kx * (c->py / 2 + 1) * zkernel_floats(c->pz) * sizeof(float) : 0},
+        {(void**)&c->ptab, (size_t)NREG * NREG * sizeof(float)},
+        {(void**)&c->params64, sizeof(mm_params)},
+        {(void**)&c->partials, (size_t)maxblk * 4 * sizeof(double)},
+        {(void**)&c->dft_tab, (size_t)2 * DFT_TABLE_BYTES},
+        {(void**)&c->tw, (size_t)c->pt * sizeof(cf)},
+        {(void**)&c->lut, NREG * sizeof(RegionLut)},
+        {(void**)&c->st, sizeof(DevState)},
+        {(void**)&c->region, (size_t)c->ncell},
+    };
+    auto slot_size = [](const Slot& s) { return (s.bytes + 255) / 256 * 256; };
+    size_t total = 0;
+    for (const Slot& s : slots) total += slot_size(s);
+    int st = map_err(dalloc(c, &c->arena, total));
+    if (st == MM_OK) {
+        char* p = static_cast<char*>(c->arena);
+        for (const Slot& s : slots) {
+            if (s.bytes) *s.p = p;
+            p += slot_size(s);
+        }
+        c->scratch_bytes = (size_t)((char*)c->spec - (char*)c->kbuf) + (size_t)c->spec_elems * sizeof(cf);
+    }
     if (st == MM_OK && hipHostMalloc((void**)&c->hst, sizeof(DevState), hipHostMallocDefault) != hipSuccess)
         st = MM_ENOMEM;
     if (st == MM_OK) st = map_err(static_scratch(c->device, &c->scratch));
@@ -872,13 +889,19 @@ int mm_create(mm_ctx** out, const mm_grid* g, const mm_params* p, const uint8_t*
 
 int mm_demag_kernel_init(mm_ctx* c) {
     if (!c) return MM_EINVAL;
-    double* oct = nullptr;
     double* win = nullptr;  // the tensor over the image window (periodic grids)
-    double2* work = nullptr;
     const bool periodic = c->pbc[0] > 0 || c->pbc[1] > 0 || c->pbc[2] > 0;
-    hipError_t e = hipMalloc((void**)&oct, (size_t)6 * c->ncell * sizeof(double));
-    if (e == hipSuccess)
-        e = hipMalloc((void**)&work, (size_t)c->px * c->py * c->pz * sizeof(double2));
+    // scratch: the stage and spectrum buffers (idle outside a step; the
+    // first-stage derivative in them is dropped below) where they are large
+    // enough, as for nearly all grids
+    const size_t noct = demag_octant_doubles(c->nx, c->ny, c->nz, c->py, c->pz);
+    const size_t need = (noct + demag_spectrum_work(c->nx, c->ny, c->nz, c->px, c->py, c->pz)) * sizeof(double);
+    double* own = nullptr;
+    hipError_t e = hipSuccess;
+    if (need > c->scratch_bytes) e = hipMalloc((void**)&own, need);
+    double* oct = own ? own : reinterpret_cast<double*>(c->kbuf);
+    double* work = oct + noct;
+    c->fsal_valid = false;
     if (e == hipSuccess && periodic)
         e = hipMalloc((void**)&win, (size_t)6 * c->win[0] * c->win[1] * c->win[2] * sizeof(double));
     if (e == hipSuccess && periodic) {
@@ -889,15 +912,13 @@ int mm_demag_kernel_init(mm_ctx* c) {
     }
     if (e == hipSuccess)
         e = demag_kernel_spectrum(c->nx, c->ny, c->nz, c->px, c->py, c->pz, oct, work, c->khat, c->ncomp,
-                                  c->kx, c->stream);
+                                  c->stream);
     if (e == hipSuccess && c->yz) e = launch_zkernel(c->khat, c->zker, (long long)c->kx * (c->py / 2 + 1), c->pz, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (oct) (void)hipFree(oct);
+    if (own) (void)hipFree(own);
     if (win) (void)hipFree(win);
-    if (work) (void)hipFree(work);
     if (e != hipSuccess) return map_err(e);
     c->khat_ready = true;
-    c->fsal_valid = false;
     return MM_OK;
 }
 
@@ -1395,8 +1416,11 @@ int mm_state_load(mm_ctx* c, const void* host_buf, int64_t bytes, const float* m
 
 int mm_demag_tensor_dump(mm_ctx* c, double* out_dev) {
     if (!c || !out_dev) return MM_EINVAL;
-    if (c->pbc[0] == 0 && c->pbc[1] == 0 && c->pbc[2] == 0)
-        return map_err(demag_tensor_octant(c->nx, c->ny, c->nz, c->dx, c->dy, c->dz, out_dev, c->stream));
+    if (c->pbc[0] == 0 && c->pbc[1] == 0 && c->pbc[2] == 0) {
+        MM_TRY(demag_tensor_octant(c->nx, c->ny, c->nz, c->dx, c->dy, c->dz, out_dev, c->stream));
+        MM_TRY(hipStreamSynchronize(c->stream));
+        return MM_OK;
+    }
     double* win = nullptr;
     hipError_t e = hipMalloc((void**)&win, (size_t)6 * c->win[0] * c->win[1] * c->win[2] * sizeof(double));
     if (e == hipSuccess) e = demag_tensor_octant(c->win[0], c->win[1], c->win[2], c->dx, c->dy, c->dz, win, c->stream);

@@ -428,23 +428,24 @@ int mm_batch_create(mm_batch** out, int32_t n, const mm_grid* grids, const mm_pa
 int mm_batch_demag_kernel_init(mm_batch* b) {
     if (!b) return MM_EINVAL;
     MM_CHECK(enter(b));
-    long long maxc = 0, maxp = 0;
+    size_t maxc = 0, maxw = 0;
     for (const BMember& m : b->hmem) {
-        const long long c = (long long)m.nx * m.ny * m.nz, p = (long long)m.px * m.py * m.pz;
+        const size_t c = demag_octant_doubles(m.nx, m.ny, m.nz, m.py, m.pz);
+        const size_t w = demag_spectrum_work(m.nx, m.ny, m.nz, m.px, m.py, m.pz);
         if (c > maxc) maxc = c;
-        if (p > maxp) maxp = p;
+        if (w > maxw) maxw = w;
     }
     double* oct = nullptr;
-    double2* work = nullptr;
-    hipError_t e = hipMalloc((void**)&oct, (size_t)6 * maxc * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void**)&work, (size_t)maxp * sizeof(double2));
+    double* work = nullptr;
+    hipError_t e = hipMalloc((void**)&oct, maxc * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc((void**)&work, maxw * sizeof(double));
     for (int i = 0; i < b->n && e == hipSuccess; ++i) {
         const BMember& m = b->hmem[i];
         const mm_grid& g = b->hgrid[i];
         e = demag_tensor_octant(m.nx, m.ny, m.nz, g.dx, g.dy, g.dz, oct, b->stream);
         if (e == hipSuccess)
             e = demag_kernel_spectrum(m.nx, m.ny, m.nz, m.px, m.py, m.pz, oct, work, b->khat + m.khat_off,
-                                      m.pz > 1 ? 6 : 4, m.kx, b->stream);
+                                      m.pz > 1 ? 6 : 4, b->stream);
         if (e == hipSuccess && m.pz > 1 && yz_supported(m.py, m.pz))
             e = launch_zkernel(b->khat + m.khat_off, b->zker + m.zker_off, (long long)m.kx * (m.py / 2 + 1), m.pz,
                                b->stream);

@@ -295,8 +295,11 @@ hipError_t demag_tensor_octant(int nx, int ny, int nz, double dx, double dy, dou
 // negative displacements by parity (win: lengths w[3] = n P or n)
 hipError_t demag_fold_images(int nx, int ny, int nz, const int* w, const int* pbc, const double* win,
                              double* oct, hipStream_t s);
-hipError_t demag_kernel_spectrum(int nx, int ny, int nz, int px, int py, int pz,
-                                 const double* octant, double2* work, float* khat, int ncomp,
-                                 int kx, hipStream_t s);
+// khat from the octant (overwritten; a buffer of demag_octant_doubles); work:
+// demag_spectrum_work doubles
+size_t demag_octant_doubles(int nx, int ny, int nz, int py, int pz);
+size_t demag_spectrum_work(int nx, int ny, int nz, int px, int py, int pz);
+hipError_t demag_kernel_spectrum(int nx, int ny, int nz, int px, int py, int pz, double* octant, double* work,
+                                 float* khat, int ncomp, hipStream_t s);
 
 }  // namespace mm
