@@ -254,14 +254,17 @@ __device__ inline void xfwd_part(const FieldArgs& a, const Resolved& rs, cf* lds
         const float im = (in && v1) ? lut_l[g1[m]].a.x * sv[MV + m] : 0.f;
         v[0][m] = mkc(re, im);
     }
+    constexpr bool IW = TPF <= 64;  // a slot's threads lie in one wave
+    // the other slots have read the finished stage's torque from this buffer
+    if constexpr (FUSED && IW) __syncthreads();
     // x >= nx is zero padding (nx <= P/2) unless the axis is unpadded
     RegFft<P, TPF, 1, false, (P >= 2 && !FULL)>::run(v, buf, a.tw, a.twshift, t);
 
     // separate the two real transforms of this slot
-    __syncthreads();
+    group_sync<IW>();
 #pragma unroll
     for (int m = 0; m < PPT; ++m) buf[lds_pad(t + TPF * m)] = v[0][m];
-    __syncthreads();
+    group_sync<IW>();
     cf X[MH], Y[MH];
 #pragma unroll
     for (int m = 0; m < MH; ++m) {
@@ -360,14 +363,15 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
         buf[lds_pad(k)] = mkc(u.x - w.y, u.y + w.x);
         if (k != 0 && 2 * k != P) buf[lds_pad(P - k)] = mkc(u.x + w.y, w.x - u.y);
     }
-    __syncthreads();
+    constexpr bool IW = TPF <= 64;  // a slot's threads lie in one wave
+    group_sync<IW>();
     cf v[1][PPT];
 #pragma unroll
     for (int m = 0; m < PPT; ++m) v[0][m] = buf[lds_pad(t + TPF * m)];
     RegFft<P, TPF, 1, true>::run(v, buf, a.tw, a.twshift, t);
     // only x < nx <= P/2 is kept (every x along an unpadded periodic axis)
     constexpr int MOUT = (P >= 2 && !FULL) ? PPT / 2 : PPT;
-    __syncthreads();
+    group_sync<IW>();
 #pragma unroll
     for (int m = 0; m < MOUT; ++m) buf[lds_pad(t + TPF * m)] = v[0][m];
     __syncthreads();
@@ -557,7 +561,7 @@ __device__ inline void col_body(const ColArgs& a, int blk, cf* lds, int tid) {
             if (i < NIT - 1 || e < TOT) reinterpret_cast<float2*>(lk6)[e] = kt[i];
         }
     }
-    RegFft<P, TPF, 1, MODE == COL_INV, HIN>::run(v, buf, a.tw, a.twshift, t);
+    RegFft<P, TPF, 1, MODE == COL_INV, HIN>::template run<!CFAST>(v, buf, a.tw, a.twshift, t);
     if (done) return;
 
     if (MODE == COL_CONV) {
@@ -684,7 +688,8 @@ __device__ inline void col_body(const ColArgs& a, int blk, cf* lds, int tid) {
             }
         }
         }
-        RegFft<P, TPF, 1, true>::run(v, buf, a.tw, a.twshift, t);
+        __syncthreads();
+        RegFft<P, TPF, 1, true>::template run<!CFAST>(v, buf, a.tw, a.twshift, t);
     }
 
     int t2 = t;
@@ -771,7 +776,7 @@ __device__ inline void yz_body(const ColArgs& a, int blk, cf* lds, int tid) {
         v[0][m] = (m < MH && valid && q < a.n_in) ? col[3LL * q] : mkc(0.f, 0.f);
     }
     RegFft<PY, TPF, 1, false, true>::run(v, buf, a.tw, a.twshift, t);
-    __syncthreads();
+    group_sync<(TPF <= 64)>();
 #pragma unroll
     for (int m = 0; m < PPT; ++m) buf[lds_pad(t + TPF * m)] = v[0][m];
     __syncthreads();
