@@ -12,6 +12,11 @@
 
 namespace mm {
 
+// No implicit contraction in this file: where a product and a sum fuse is
+// written out, so every instance of a transform (tile shapes, components per
+// thread, single grids and ensembles) rounds alike.
+#pragma clang fp contract(off)
+
 struct alignas(8) cf {
     float x, y;
 };
@@ -21,7 +26,14 @@ __host__ __device__ inline cf operator+(cf a, cf b) { return mkc(a.x + b.x, a.y 
 __host__ __device__ inline cf operator-(cf a, cf b) { return mkc(a.x - b.x, a.y - b.y); }
 __host__ __device__ inline cf operator*(float s, cf a) { return mkc(s * a.x, s * a.y); }
 __host__ __device__ inline cf cmul(cf a, cf b) {
-    return mkc(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return mkc(__builtin_fmaf(-a.y, b.y, a.x * b.x), __builtin_fmaf(a.y, b.x, a.x * b.y));
+}
+// a + s b with a real s, and k0 a + k1 b + k2 c with real k
+__host__ __device__ inline cf cfma(float s, cf b, cf a) {
+    return mkc(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y));
+}
+__host__ __device__ inline cf crow3(float k0, cf a, float k1, cf b, float k2, cf c) {
+    return cfma(k2, c, cfma(k1, b, k0 * a));
 }
 __host__ __device__ inline cf cconj(cf a) { return mkc(a.x, -a.y); }
 
@@ -39,6 +51,16 @@ __device__ inline cf ld_cf(const cf* base, unsigned int byte_off) {
 __device__ inline void st_cf(cf* base, unsigned int byte_off, cf v) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), cf_buffer(base), (int)byte_off, 0, 0);
+}
+
+// Two adjacent complex values.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ inline f32x4 ld_cf2(const cf* base, unsigned int byte_off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(cf_buffer(base), (int)byte_off, 0, 0));
+}
+__device__ inline void st_cf2(cf* base, unsigned int byte_off, f32x4 v) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), cf_buffer(base), (int)byte_off, 0, 0);
 }
 
 // multiply by exp(+-i pi/2): forward (INV=false) by -i, inverse by +i
@@ -102,15 +124,19 @@ struct Dft<8, INV> {
         cf o[4] = {v[1], v[3], v[5], v[7]};
         Dft<4, INV>::run(e);
         Dft<4, INV>::run(o);
-        // o[k] *= w8^k with w8 = exp(-+ i pi/4)
-        cf o1 = o[1], o3 = o[3];
-        o[1] = INV ? mkc(h * (o1.x - o1.y), h * (o1.x + o1.y)) : mkc(h * (o1.x + o1.y), h * (o1.y - o1.x));
-        o[2] = rot90<INV>(o[2]);
-        o[3] = INV ? mkc(-h * (o3.x + o3.y), h * (o3.x - o3.y)) : mkc(h * (o3.y - o3.x), -h * (o3.x + o3.y));
-        for (int k = 0; k < 4; ++k) {
-            v[k] = e[k] + o[k];
-            v[k + 4] = e[k] - o[k];
-        }
+        // v[k], v[k + 4] = e[k] +- w8^k o[k] with w8 = exp(-+ i pi/4); the factor
+        // 1/sqrt(2) of k = 1, 3 goes into fused multiply-adds
+        const cf o2 = rot90<INV>(o[2]);
+        const cf p1 = INV ? mkc(o[1].x - o[1].y, o[1].x + o[1].y) : mkc(o[1].x + o[1].y, o[1].y - o[1].x);
+        const cf p3 = INV ? mkc(-(o[3].x + o[3].y), o[3].x - o[3].y) : mkc(o[3].y - o[3].x, -(o[3].x + o[3].y));
+        v[0] = e[0] + o[0];
+        v[4] = e[0] - o[0];
+        v[1] = cfma(h, p1, e[1]);
+        v[5] = cfma(-h, p1, e[1]);
+        v[2] = e[2] + o2;
+        v[6] = e[2] - o2;
+        v[3] = cfma(h, p3, e[3]);
+        v[7] = cfma(-h, p3, e[3]);
     }
 };
 
@@ -431,5 +457,7 @@ struct RegFft {
         finish(v);
     }
 };
+
+#pragma clang fp contract(fast)
 
 }  // namespace mm

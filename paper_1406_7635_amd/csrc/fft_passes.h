@@ -20,9 +20,8 @@
 //               m_s = m0 + dt sum a k, M = Msat[region] m_s, FFT along x of
 //               the zero-padded rows, separation of the two real transforms
 //               X = (Z[k] + conj Z[P-k])/2, Y = (Z[k] - conj Z[P-k])/(2i);
-//   column    : per column, one thread group per component: FFT along y (3D:
-//               forward and inverse around the z pass), or forward FFT,
-//               B^_i = sum_j K^_ij M^_j through LDS (K^ real symmetric, one
+//   column    : FFT along y (3D: forward and inverse around the z pass), or
+//               forward FFT, B^_i = sum_j K^_ij M^_j (K^ real symmetric, one
 //               octant stored, mirror signs applied), inverse FFT.  In 2D the
 //               DC and Nyquist columns (both real along y) share one complex
 //               column;
@@ -31,6 +30,8 @@
 //               Zeeman, torque, error norm, energies).
 // The 1/(px py pz) normalisation and -mu0 are folded into K^.
 #pragma once
+
+#include <type_traits>
 
 #include "field_epilogue.h"
 
@@ -421,8 +422,10 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
 }
 
 // ---------------------------------------------------------------------------
-// Column pass.  Threads: (column ci < T, component s < 3, t < TPF); with
-// CFAST the column index varies fastest over the lanes (strided columns, so
+// Column pass with a thread group per component: the 2D convolution of the
+// lengths that col3_body does not serve, and the y transforms and z convolution
+// of small 3D grids (column_split below).
+// Threads: (column ci < T, component s < 3, t < TPF); with CFAST the column index varies fastest over the lanes (strided columns, so
 // neighbouring lanes read neighbouring columns), else t does (contiguous
 // columns).
 // LDS elements per sequence of the column pass.  With CFAST the lanes of a
@@ -602,7 +605,7 @@ __device__ inline void col_body(const ColArgs& a, int blk, cf* lds, int tid) {
                 const float s1 = ((fa && odd_y(j1)) != (fq && odd_z(j1))) ? -1.f : 1.f;
                 const float s2 = ((fa && odd_y(j2)) != (fq && odd_z(j2))) ? -1.f : 1.f;
                 const cf m0 = bufs[lds_pad(q)], m1 = bufs[SEQ + lds_pad(q)], m2 = bufs[2 * SEQ + lds_pad(q)];
-                const cf b = (s0 * K[j0]) * m0 + (s1 * K[j1]) * m1 + (s2 * K[j2]) * m2;
+                const cf b = crow3(s0 * K[j0], m0, s1 * K[j1], m1, s2 * K[j2], m2);
                 v[0][m] = valid ? b : mkc(0.f, 0.f);
             }
         } else {
@@ -838,6 +841,333 @@ __device__ inline void yz_body(const ColArgs& a, int blk, cf* lds, int tid) {
     for (int m = 0; m < MH; ++m) {
         const int q = t2 + TPF * m;
         if (valid && q < a.n_in) col[3LL * q] = v[0][m];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Staged columns (three components per thread) serve the y transforms and the z
+// convolution of 3D grids that give every SIMD of the chip a wave this way:
+// columns x threads per column >= 65536.  Below that the pass is a chain of
+// latencies, which a thread group per component (col_body) shortens: 64 x 64 x 8
+// field 29.0 against 31.1 us, 33 x 17 x 9 25.6 against 30.4; above it the staged
+// form wins, 200 x 200 x 30 165 against 196 us, 40 x 300 x 20 72 against 82.
+inline bool column_split(int p, long long columns) {
+    const int tpf = p >= 4096 ? p / 16 : (p >= 8 ? p / 8 : 1);
+    return columns * tpf < 65536;
+}
+
+// The address unit takes 16 cycles for a wave's access to
+// adjacent lanes, but nearly one per lane at the 24-byte stride of a spectrum
+// element (counted: 47 cache accesses per 8-byte load, 80 % of the z
+// convolution's time), so the 3D column passes move runs of elements as 16-byte
+// chunks of adjacent lanes and transpose through LDS.  v0, v1: which of the
+// chunk's two complex values exist (one that straddles the end of a run moves
+// the half that is inside).
+__device__ inline f32x4 chunk_load(const cf* base, unsigned int off, bool v0, bool v1) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (v0 && v1) {
+        v = ld_cf2(base, off);
+    } else if (v0) {
+        const cf x = ld_cf(base, off);
+        v[0] = x.x;
+        v[1] = x.y;
+    } else if (v1) {
+        const cf x = ld_cf(base, off + 8u);
+        v[2] = x.x;
+        v[3] = x.y;
+    }
+    return v;
+}
+__device__ inline void chunk_store(cf* base, unsigned int off, bool v0, bool v1, f32x4 v) {
+    if (v0 && v1)
+        st_cf2(base, off, v);
+    else if (v0)
+        st_cf(base, off, mkc(v[0], v[1]));
+    else if (v1)
+        st_cf(base, off + 8u, mkc(v[2], v[3]));
+}
+
+// ---------------------------------------------------------------------------
+// 3D z convolution: forward FFT along z of every (kx, ky) column, B^ = K^ M^
+// (6 components), inverse FFT.  A thread carries the three components of its
+// points, so the product needs no exchange, and addresses, signs and
+// multipliers of a stage serve all three.  A tile takes TH columns ky from
+// kyh0 = tile TH on below py/2 and the TH columns from py - kyh0 - TH on, the
+// mirrors of kyh0 + 1 ... kyh0 + TH: two aligned runs per plane, every column once,
+// and each K^ block read once (but for the one that adjacent tiles share).
+//
+// What bounds it: with a thread group per component and 8-byte accesses, the
+// vector unit (products through LDS, addresses and twiddles formed three
+// times) and the address unit; now the vector unit and the 507 MB share the
+// time.  256 x 256 x 64 (P = 128): 150 -> 117 us; 150 x 90 x 37: 79 -> 56 us.
+template <int P>
+struct ZCfg {
+    static constexpr int TPF = Cfg<P>::TPF, PPT = Cfg<P>::PPT;
+    static constexpr int T = TPF >= 256 ? 1 : 256 / TPF;  // columns per workgroup
+    static constexpr int NTH = T * TPF;
+    static constexpr bool PAIR = T >= 2;
+    static constexpr int TH = PAIR ? T / 2 : 1;           // columns per run
+    static constexpr int NK = PAIR ? TH + 1 : 1;          // K^ blocks per tile
+    static constexpr int KHP = P / 2 + 1, MH = P / 2;     // K^ rows; planes that hold data (P >= 2 nz)
+    static constexpr int SEQ = seq_len(P);
+    static constexpr int RUNS = PAIR ? 2 : 1, CR = (3 * TH + 1) / 2;  // runs per plane, chunks per run
+    // chunks per plane; planes per step, or steps per plane where a plane has
+    // more chunks than the workgroup threads
+    static constexpr int CH = CR * RUNS, ZPS = CH <= NTH ? NTH / CH : 1, WPT = (CH + NTH - 1) / NTH;
+    // staging pitch of a plane, odd: 16 lanes a plane apart meet no bank conflict
+    static constexpr int PITCH = 2 * CH + 1;
+    static constexpr int KOFF = T * SEQ + ((T * SEQ) & 1);
+    static constexpr int LDS1 = KOFF + NK * KHP * 3, LDS2 = MH * PITCH + 1;
+    static constexpr int LDS = LDS1 > LDS2 ? LDS1 : LDS2;  // complex elements
+};
+template <int P>
+constexpr size_t z_lds() { return (size_t)ZCfg<P>::LDS * sizeof(cf); }
+// tiles per kx of ncol = py columns
+template <int P>
+__host__ __device__ constexpr int z_ntile(int ncol) {
+    using C = ZCfg<P>;
+    return C::PAIR ? ((ncol > 1 ? ncol / 2 : 1) + C::TH - 1) / C::TH : ncol;
+}
+
+template <int P>
+__device__ inline void zconv_body(const ColArgs& a, int blk, cf* lds, int tid) {
+    using C = ZCfg<P>;
+    constexpr int TPF = C::TPF, PPT = C::PPT, T = C::T, TH = C::TH, KHP = C::KHP, SEQ = C::SEQ, PITCH = C::PITCH;
+    constexpr int MH = PPT / 2;
+    // a finished run is tested after the forward transform (nothing is
+    // written before), so the state read overlaps the column loads
+    const int done = a.check_done ? a.st->done : 0;
+    const int ntile = z_ntile<P>(a.ncol);
+    const int kx = blk / ntile, tile = blk - kx * ntile;
+    // the kx slab (uniform) and 32-bit offsets within it: at most 2048 x 4096 x 3 complex
+    cf* slab = a.spec + (long long)kx * a.outer_stride;
+    // runs of this tile: complex elements [lo, hi) valid of the 3 TH from column c0 on
+    const int half = a.ncol / 2, kyh0 = C::PAIR ? tile * TH : 0;
+    int c0[2], lo[2], hi[2];
+    if constexpr (C::PAIR) {
+        const int left = (a.ncol > 1 ? half : 1) - kyh0;  // columns of the first run
+        c0[0] = kyh0;
+        lo[0] = 0;
+        hi[0] = 3 * (left < TH ? left : TH);
+        c0[1] = a.ncol - kyh0 - TH;
+        lo[1] = a.ncol > 1 ? (half - kyh0 < TH ? 3 * (TH - (half - kyh0)) : 0) : 3 * TH;
+        hi[1] = 3 * TH;
+    } else {
+        c0[0] = c0[1] = tile;
+        lo[0] = lo[1] = hi[1] = 0;
+        hi[0] = 3;
+    }
+    // planes z < n_in (<= P/2) into LDS, run r at 2 CR r of a plane's pitch: a
+    // thread's chunks within a plane (run r, elements e, e + 1) are fixed, z
+    // advances by ZPS
+    constexpr int CR = C::CR, CH = C::CH, ZPS = C::ZPS, WPT = C::WPT, NIT = (C::MH + ZPS - 1) / ZPS;
+    const int z0 = CH <= C::NTH ? tid / CH : 0;
+    const int w0 = tid - z0 * CH;
+    bool mv[WPT], v0[WPT], v1[WPT];
+    unsigned int goff[WPT];
+    const unsigned int ps8 = (unsigned int)a.pos_stride * 8u;
+#pragma unroll
+    for (int j = 0; j < WPT; ++j) {
+        const int w = w0 + C::NTH * j, r = C::PAIR && w >= CR ? 1 : 0, e = 2 * (w - r * CR);
+        const int l = r ? lo[1] : lo[0], h = r ? hi[1] : hi[0], c = r ? c0[1] : c0[0];
+        mv[j] = z0 < ZPS && w < CH;
+        v0[j] = mv[j] && e >= l && e < h;
+        v1[j] = mv[j] && e + 1 >= l && e + 1 < h;
+        goff[j] = (unsigned int)z0 * ps8 + (unsigned int)(3 * c + e) * 8u;
+    }
+    cf* zst = lds + z0 * PITCH + 2 * w0;  // chunk j of plane z0 + ZPS i at + 2 NTH j + ZPS i PITCH
+    {
+        f32x4 st[NIT][WPT];
+#pragma unroll
+        for (int i = 0; i < NIT; ++i)
+#pragma unroll
+            for (int j = 0; j < WPT; ++j) {
+                const bool in = z0 + ZPS * i < a.n_in;
+                st[i][j] = chunk_load(slab, goff[j] + (unsigned int)(ZPS * i) * ps8, in && v0[j], in && v1[j]);
+            }
+#pragma unroll
+        for (int i = 0; i < NIT; ++i)
+#pragma unroll
+            for (int j = 0; j < WPT; ++j)
+                if (mv[j] && (C::MH % ZPS == 0 || z0 + ZPS * i < C::MH)) {
+                    cf* q = zst + 2 * C::NTH * j + ZPS * i * PITCH;
+                    q[0] = mkc(st[i][j][0], st[i][j][1]);
+                    q[1] = mkc(st[i][j][2], st[i][j][3]);
+                }
+    }
+    // the tile's K^ blocks (all kz, 6 components, contiguous), on their way
+    // during the forward transform
+    constexpr int BL = KHP * 3, TOT = C::NK * BL, NIK = (TOT + C::NTH - 1) / C::NTH;  // float2s
+    const bool mir1 = 2 * tile > a.ncol;  // single columns: the mirrored half
+    const int kb0 = C::PAIR ? kyh0 : (mir1 ? a.ncol - tile : tile);
+    const int nky = half + 1 - kb0;  // blocks of this kx from kb0 on
+    const cf* kslab = reinterpret_cast<const cf*>(a.khat + ((long long)kx * a.kyh + kb0) * (KHP * 6));
+    cf kt[NIK];
+#pragma unroll
+    for (int i = 0; i < NIK; ++i) {
+        const int e = tid + C::NTH * i;
+        kt[i] = ((i < NIK - 1 || e < TOT) && e < nky * BL) ? ld_cf(kslab, (unsigned int)e * 8u) : mkc(0.f, 0.f);
+    }
+    const int ci = tid / TPF, t = tid % TPF;
+    const bool mir = C::PAIR ? ci >= TH : mir1;
+    // the column's place in a plane, and its K^ block in the tile
+    const int col = C::PAIR && mir ? 2 * CR + 3 * (ci - TH) : 3 * ci;
+    const int kb = C::PAIR ? (mir ? 2 * TH - ci : ci) : 0;
+    __syncthreads();
+    cf v[3][PPT];
+#pragma unroll
+    for (int m = 0; m < PPT; ++m) {
+        const cf* p = lds + (t + TPF * m) * PITCH + col;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k][m] = m < MH ? p[k] : mkc(0.f, 0.f);
+    }
+    __syncthreads();
+    cf* buf = lds + ci * SEQ;
+    cf* lk = lds + C::KOFF;
+    RegFft<P, TPF, 3, false, (P >= 2)>::run(v, buf, a.tw, a.twshift, t);
+    if (done) return;
+#pragma unroll
+    for (int i = 0; i < NIK; ++i) {
+        const int e = tid + C::NTH * i;
+        if (i < NIK - 1 || e < TOT) lk[e] = kt[i];
+    }
+    __syncthreads();
+    // xy and yz are odd in y, xz and yz in z (all 0 where an axis is at P/2, so
+    // the sign there is free)
+    const float sy = mir ? -1.f : 1.f;
+    const cf* Kb = lk + kb * BL;
+#pragma unroll
+    for (int m = 0; m < PPT; ++m) {
+        const int q = t + TPF * m;
+        const bool fq = PPT > 1 ? m >= MH : 2 * q > P;
+        const cf* K = Kb + (fq ? P - q : q) * 3;
+        const cf k0 = K[0], k1 = K[1], k2 = K[2];
+        const float kxx = k0.x, kyy = k0.y, kzz = k1.x, kxy = sy * k1.y, kxz = fq ? -k2.x : k2.x,
+                    kyz = sy * (fq ? -k2.y : k2.y);
+        const cf mx = v[0][m], my = v[1][m], mz = v[2][m];
+        v[0][m] = crow3(kxx, mx, kxy, my, kxz, mz);
+        v[1][m] = crow3(kxy, mx, kyy, my, kyz, mz);
+        v[2][m] = crow3(kxz, mx, kyz, my, kzz, mz);
+    }
+    int ti = t;
+    asm volatile("" : "+v"(ti));  // the inverse transform derives its addresses afresh
+    RegFft<P, TPF, 3, true>::run(v, buf, a.tw, a.twshift, ti);
+    __syncthreads();  // the planes go where other columns' exchanges and K^ were
+#pragma unroll
+    for (int m = 0; m < MH; ++m) {
+        cf* p = lds + (t + TPF * m) * PITCH + col;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k] = v[k][m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NIT; ++i)
+#pragma unroll
+        for (int j = 0; j < WPT; ++j)
+            if (z0 + ZPS * i < a.n_out && mv[j]) {
+                const cf* q = zst + 2 * C::NTH * j + ZPS * i * PITCH;
+                const cf x = q[0], y = q[1];
+                chunk_store(slab, goff[j] + (unsigned int)(ZPS * i) * ps8, v0[j], v1[j], f32x4{x.x, x.y, y.x, y.y});
+            }
+}
+
+// ---------------------------------------------------------------------------
+// y transforms of 3D grids, in place: MODE COL_FWD (n_in rows -> P rows) or
+// COL_INV (P rows -> n_out rows).  A column (kx, z) is one run of 3 P complex
+// elements; a thread carries its three components.  For lengths up to 512 a
+// column's 64 threads or fewer share a wave, so a wave stages and transforms its
+// columns without workgroup barriers.  256 x 256 x 64 (P = 512, 303 MB each):
+// forward 78 -> 58 us, inverse 55 -> 49 us.
+template <int P>
+struct YCfg {
+    static constexpr int TPF = Cfg<P>::TPF, PPT = Cfg<P>::PPT;
+    static constexpr int T = TPF >= 256 ? 1 : 256 / TPF;     // columns per workgroup
+    static constexpr int NTH = T * TPF;
+    static constexpr bool WAVE = TPF <= 64;
+    static constexpr int GT = WAVE ? 64 : NTH, GC = GT / TPF;  // threads, columns that stage together
+    // pitch of a column's elements: 16-byte aligned, columns in different banks
+    static constexpr int PITCH = 3 * P + (P & 1) + 2;
+    static constexpr int LDS = T * PITCH;
+};
+template <int P>
+constexpr size_t y_lds() { return (size_t)YCfg<P>::LDS * sizeof(cf); }
+template <int P>
+__host__ __device__ constexpr int y_ntile(int ncol) { return (ncol + YCfg<P>::T - 1) / YCfg<P>::T; }
+
+template <int P, int MODE>
+__device__ inline void ycol_body(const ColArgs& a, int blk, cf* lds, int tid) {
+    using C = YCfg<P>;
+    constexpr int TPF = C::TPF, PPT = C::PPT, GT = C::GT, GC = C::GC, PITCH = C::PITCH;
+    constexpr bool FWD = MODE == COL_FWD, W = C::WAVE;
+    constexpr int MI = FWD && P >= 2 ? PPT / 2 : PPT;     // registers that hold input
+    constexpr int MO = !FWD && P >= 2 ? PPT / 2 : PPT;    // registers that are kept
+    const int done = a.check_done ? a.st->done : 0;
+    const int ntile = y_ntile<P>(a.ncol);
+    const int o = blk / ntile, tile = blk - o * ntile;
+    cf* slab = a.spec + (long long)o * a.outer_stride;    // a kx slab (uniform), 32-bit offsets within it
+    const int g = tid / GT, gt = tid % GT;                // staging group and the thread within it
+    const int col0 = tile * C::T + g * GC;                // its first column
+    cf* gl = lds + g * GC * PITCH;
+    // chunk i of the thread: column of the group, element, first element of the column
+    auto chunk = [&](auto per, int i, int gt, int& cc, int& e) {
+        constexpr int CH = decltype(per)::value;          // chunks per column
+        if constexpr (CH % GT == 0) {
+            cc = GT * i / CH;
+            e = 2 * (gt + GT * i - cc * CH);
+            return true;
+        } else {
+            const int u = gt + GT * i;
+            cc = u / CH;
+            e = 2 * (u - cc * CH);
+            return (GC * CH) % GT == 0 || i < (GC * CH) / GT || u < GC * CH;
+        }
+    };
+    auto off = [&](int cc, int e) {
+        return ((unsigned int)(col0 + cc) * (unsigned int)a.col_stride + (unsigned int)e) * 8u;
+    };
+    constexpr int CHI = (3 * MI * TPF + 1) / 2, NI = (GC * CHI + GT - 1) / GT;
+    constexpr int CHO = (3 * MO * TPF + 1) / 2, NO = (GC * CHO + GT - 1) / GT;
+    {
+        f32x4 st[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            int cc, e;
+            st[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (chunk(std::integral_constant<int, CHI>{}, i, gt, cc, e) && col0 + cc < a.ncol)
+                st[i] = chunk_load(slab, off(cc, e), e < 3 * a.n_in, e + 1 < 3 * a.n_in);
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            int cc, e;
+            if (chunk(std::integral_constant<int, CHI>{}, i, gt, cc, e))
+                *reinterpret_cast<f32x4*>(gl + cc * PITCH + e) = st[i];
+        }
+    }
+    const int ci = gt / TPF, t = gt % TPF;
+    cf* buf = gl + ci * PITCH;  // the column's elements, then its exchanges
+    group_sync<W>();
+    cf v[3][PPT];
+#pragma unroll
+    for (int m = 0; m < PPT; ++m)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k][m] = m < MI ? buf[3 * (t + TPF * m) + k] : mkc(0.f, 0.f);
+    group_sync<W>();
+    RegFft<P, TPF, 3, !FWD, FWD && (P >= 2)>::run(v, buf, a.tw, a.twshift, t);
+    if (done) return;
+    group_sync<W>();
+#pragma unroll
+    for (int m = 0; m < MO; ++m)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) buf[3 * (t + TPF * m) + k] = v[k][m];
+    group_sync<W>();
+    int go = gt;
+    asm volatile("" : "+v"(go));  // form the store addresses here, not at load time
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        int cc, e;
+        if (chunk(std::integral_constant<int, CHO>{}, i, go, cc, e) && col0 + cc < a.ncol)
+            chunk_store(slab, off(cc, e), e < 3 * a.n_out, e + 1 < 3 * a.n_out,
+                        *reinterpret_cast<const f32x4*>(gl + cc * PITCH + e));
     }
 }
 

@@ -88,6 +88,19 @@ __global__ void __launch_bounds__(ColCfg<P>::NTH) k_col(const ColArgs a) {
     col_body<P, MODE, NC, CFAST>(a, xcd_remap(blockIdx.x, gridDim.x), lds, threadIdx.x);
 }
 
+template <int P, int MODE>
+__global__ void __launch_bounds__(YCfg<P>::NTH) k_ycol(const ColArgs a) {
+    extern __shared__ cf lds[];
+    ycol_body<P, MODE>(a, xcd_remap(blockIdx.x, gridDim.x), lds, threadIdx.x);
+}
+
+template <int P>
+__global__ void __launch_bounds__(ZCfg<P>::NTH) __attribute__((amdgpu_waves_per_eu(P >= 4096 ? 2 : 4)))
+k_zconv(const ColArgs a) {
+    extern __shared__ cf lds[];
+    zconv_body<P>(a, xcd_remap(blockIdx.x, gridDim.x), lds, threadIdx.x);
+}
+
 template <int P, bool FULL, int W>
 __global__ void __launch_bounds__((Col3Cfg<P, W>::NTH), 4) k_col3(const ColArgs a) {
     extern __shared__ cf lds[];
@@ -193,6 +206,21 @@ static hipError_t xrow_p(const FieldArgs& ai, const FieldArgs& af, float a_last,
     return x_width<P>(ai.nrows) ? xrow_pw<P, 1>(ai, af, a_last, s, e0, e1) : xrow_pw<P, 0>(ai, af, a_last, s, e0, e1);
 }
 
+template <int P>
+static hipError_t zconv_p(const ColArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const long long nb = (long long)z_ntile<P>(a.ncol) * a.nouter;
+    hipExtLaunchKernelGGL((k_zconv<P>), dim3((unsigned)nb), dim3(ZCfg<P>::NTH), (uint32_t)z_lds<P>(), s, e0, e1, 0, a);
+    return hipGetLastError();
+}
+
+template <int P, int MODE>
+static hipError_t ycol_p(const ColArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const long long nb = (long long)y_ntile<P>(a.ncol) * a.nouter;
+    hipExtLaunchKernelGGL((k_ycol<P, MODE>), dim3((unsigned)nb), dim3(YCfg<P>::NTH), (uint32_t)y_lds<P>(), s, e0, e1, 0,
+                          a);
+    return hipGetLastError();
+}
+
 template <int P, int MODE, int NC, bool CFAST>
 static hipError_t col_p(const ColArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const size_t lds = col_lds<P, MODE, NC, CFAST>();
@@ -229,6 +257,8 @@ static hipError_t col3_p(const ColArgs& a, hipStream_t s, hipEvent_t e0, hipEven
     return col3_pw<P, 0>(a, s, e0, e1);
 }
 
+// padded z lengths of 3D grids (2 layers pad to 4)
+#define MM_ZCASES(M) M(4) M(8) M(16) M(32) M(64) M(128) M(256) M(512) M(1024) M(2048) M(4096)
 #define MM_CASES(M) M(1) M(2) M(4) M(8) M(16) M(32) M(64) M(128) M(256) M(512) M(1024) M(2048) M(4096)
 
 template <int P>
@@ -364,13 +394,17 @@ static hipError_t configure_col(bool three_d) {
         }
         return allow_lds<P>((const void*)k_col<P, COL_CONV, 4, false>, col_lds<P, COL_CONV, 4>());
     }
-    hipError_t e = allow_lds<P>((const void*)k_col<P, COL_FWD, 4, false>, col_lds<P, COL_FWD, 4>());
+    hipError_t e = allow_lds<P>((const void*)k_ycol<P, COL_FWD>, y_lds<P>());
+    if (e == hipSuccess) e = allow_lds<P>((const void*)k_ycol<P, COL_INV>, y_lds<P>());
+    if (e == hipSuccess) e = allow_lds<P>((const void*)k_col<P, COL_FWD, 4, false>, col_lds<P, COL_FWD, 4>());
     if (e == hipSuccess) e = allow_lds<P>((const void*)k_col<P, COL_INV, 4, false>, col_lds<P, COL_INV, 4>());
     return e;
 }
 
 template <int P>
 static hipError_t configure_zconv(void) {
+    const hipError_t e = allow_lds<P>((const void*)k_zconv<P>, z_lds<P>());
+    if (e != hipSuccess) return e;
     return allow_lds<P>((const void*)k_col<P, COL_CONV, 6, true>, col_lds<P, COL_CONV, 6, true>());
 }
 
@@ -404,7 +438,7 @@ hipError_t configure_field_kernels(int px, int py, int pz) {
     case p:                     \
         e = configure_zconv<p>(); \
         break;
-        MM_CASES(M)
+        MM_ZCASES(M)
 #undef M
         default:
             return hipErrorInvalidValue;
@@ -463,11 +497,12 @@ hipError_t launch_xinv(int px, const FieldArgs& a, hipStream_t s, int* nb_out, h
 }
 
 hipError_t launch_col(int p, int mode, const ColArgs& a, int ncomp, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const long long cols = (long long)a.ncol * a.nouter;
     if (mode == COL_FWD) {
         switch (p) {
 #define M(q) \
     case q:  \
-        return col_p<q, COL_FWD, 4, false>(a, s, e0, e1);
+        return column_split(q, cols) ? col_p<q, COL_FWD, 4, false>(a, s, e0, e1) : ycol_p<q, COL_FWD>(a, s, e0, e1);
             MM_CASES(M)
 #undef M
             default:
@@ -478,7 +513,7 @@ hipError_t launch_col(int p, int mode, const ColArgs& a, int ncomp, hipStream_t 
         switch (p) {
 #define M(q) \
     case q:  \
-        return col_p<q, COL_INV, 4, false>(a, s, e0, e1);
+        return column_split(q, cols) ? col_p<q, COL_INV, 4, false>(a, s, e0, e1) : ycol_p<q, COL_INV>(a, s, e0, e1);
             MM_CASES(M)
 #undef M
             default:
@@ -500,8 +535,8 @@ hipError_t launch_col(int p, int mode, const ColArgs& a, int ncomp, hipStream_t 
     switch (p) {
 #define M(q) \
     case q:  \
-        return col_p<q, COL_CONV, 6, true>(a, s, e0, e1);
-        MM_CASES(M)
+        return column_split(q, cols) ? col_p<q, COL_CONV, 6, true>(a, s, e0, e1) : zconv_p<q>(a, s, e0, e1);
+        MM_ZCASES(M)
 #undef M
         default:
             return hipErrorInvalidValue;
