@@ -121,6 +121,39 @@ struct Staged {
     }
 };
 
+// The same copy in 16-byte chunks (two complex) for whole row pairs (ny even:
+// both rows exist, in one plane, so a pair's six values per kx are one run).
+template <int P, int W = 0>
+struct StagedPairs {
+    static constexpr int GI = XCfg<P, W>::GI, NTH = XCfg<P, W>::NTH, KH = XCfg<P, W>::KH, GL = XCfg<P, W>::GL;
+    static constexpr int TOT = GI * KH * 3, NIT = (TOT + NTH - 1) / NTH, KS = NTH / 3;
+    static_assert(NTH % 3 == 0 && GL % 2 == 0, "chunks per row pair");
+    int ch, kq0;
+    __device__ explicit StagedPairs(int tid) : ch(tid % 3), kq0(tid / 3) {}
+    // chunk i of the thread: LDS index (-1: none), and spectrum offset (-1: none,
+    // or its pair is past the grid)
+    __device__ void at(const FieldArgs& a, const long long* rbs, int i, int& lidx, long long& off) const {
+        const int kq = kq0 + KS * i;
+        const int gg = GI == 1 ? 0 : kq / KH;
+        const int k = kq - gg * KH;
+        const bool in = i < NIT - 1 || kq < GI * KH;
+        lidx = in ? gg * GL + 6 * k + 2 * ch : -1;
+        const long long rb = in ? rbs[2 * gg] : -1;
+        off = rb >= 0 ? rb + (long long)k * a.colstride + 2 * ch : -1;
+    }
+};
+
+// Whether the x passes move the spectrum two elements and combine four cells per
+// thread and access (Q4): a wave's access takes the address unit 16 cycles
+// whatever its width.  The forward pass gains at both workgroup widths (1024^2
+// film 20.9 -> 19.2 us, 64^2 film 7.0 -> 5.9 us); the inverse and fused passes at
+// the narrow one (64^2 film: fused 12.1 -> 10.9 us, inverse 10.6 -> 9.7 us), while
+// wide workgroups hide the accesses behind each other and lose the free half of
+// the slot buffers (fused: 1024^2 film 38.4 -> 38.2 us, 512^2 x 16 with 16 regions
+// 182 -> 186 us).  Rows are whole groups of four cells and pairs of rows;
+// nx = 4 pads to 8, and shorter lengths (periodic rows) keep the other form.
+inline bool x_quads(int px, int nx, int ny, bool dmi) { return px >= 8 && nx % 4 == 0 && ny % 2 == 0 && !dmi; }
+
 // ---------------------------------------------------------------------------
 // x passes.  Both stage the region table in LDS after the row-pair area.
 template <int P, int W = 0>
@@ -146,7 +179,7 @@ struct XLut {
 // stage's combine through LDS.  Padded x: component c of a row pair's two rows
 // ([row][x], floats) in the upper half of slot buffer c, which the x-inverse
 // results (x < nx <= P/2, the lower half) leave free.  Unpadded periodic x
-// (FULL: nx = P, no free half): in place of the cell's own x-inverse result,
+// (FULL: nx = P, no free half), and Q4: in place of the cell's own x-inverse result,
 // which only that cell's epilogue reads (components x, y of row rr in slot
 // rr; z of both rows in slot 2, row rr in its float rr).  Needs P >= 2.
 template <int P>
@@ -168,7 +201,7 @@ __device__ inline float* k_slot(cf* gbuf, int c, int rr, int x, int nx) {
 // zero-padded rows, separation of the two real transforms, staged coalesced
 // spectrum write.  The region table is in LDS at lut_l once the first barrier
 // has passed (the non-fused pass writes it from lut after issuing its loads).
-template <int P, bool FUSED, bool FULL = false, int XW = 0>
+template <int P, bool FUSED, bool FULL = false, int XW = 0, bool Q4 = false>
 __device__ inline void xfwd_part(const FieldArgs& a, const Resolved& rs, cf* lds, const long long* rbs,
                                  RegionLut* lut_l, const XLut<P, XW>* lut, float a_last, int blk, int tid) {
     constexpr int PPT = Cfg<P>::PPT, TPF = Cfg<P>::TPF, GI = XCfg<P, XW>::GI;
@@ -186,78 +219,130 @@ __device__ inline void xfwd_part(const FieldArgs& a, const Resolved& rs, cf* lds
     cf* buf = gbuf + slot * SEQ;
     const long long n = a.ncell;
 
-    // slot 0: (x, y) of row a, slot 1: (x, y) of row b, slot 2: z of rows a and b
-    const int r0 = slot == 1 ? rb : ra;
-    const bool v0 = slot == 1 ? vb : va;
-    const int c0 = slot == 2 ? 2 : 0;
-    const int r1 = slot == 0 ? ra : rb;
-    const bool v1 = slot == 0 ? va : vb;
-    const int c1 = slot == 2 ? 2 : 1;
-    const int rr0 = slot == 1 ? 1 : 0, rr1 = slot == 0 ? 0 : 1;  // rows within the pair
-
     // Only x < P/2 can hold cells (P >= 2 nx - 1), except along an unpadded
-    // periodic axis (FULL: P = nx); rows and columns past the grid are clamped
-    // for the loads and masked afterwards, so every load of the thread is
-    // issued before the first one is used.
+    // periodic axis (FULL: P = nx).
     constexpr int MV = FULL ? PPT : (PPT > 1 ? PPT / 2 : 1);
-    const int r0c = v0 ? r0 : 0, r1c = v1 ? r1 : 0;
     cf v[1][PPT];
 #pragma unroll
     for (int m = MV; m < PPT; ++m) v[0][m] = mkc(0.f, 0.f);
-    unsigned int idx0[MV], idx1[MV];  // byte offsets into the [3][ncell] arrays
-    int g0[MV], g1[MV];
+    if constexpr (Q4) {
+        // four cells of one component of one row per step: the combine, m_s, and
+        // M to its place in the slot buffers (component, row) -> (slot, part), from
+        // where the transform takes its points.  (FUSED: the finished stage's
+        // torque waits in that very place.)
+        constexpr int MQ = FULL ? P / 4 : P / 8, TG = 3 * TPF, NQ = (6 * MQ + TG - 1) / TG;
+        const int nq = a.nx >> 2, tg = tid % TG;
+        auto place = [&](int u, int& c, int& rr, int& x) {  // task u of the row pair
+            const int cr = u / MQ;
+            c = cr >> 1;
+            rr = cr & 1;
+            x = 4 * (u - cr * MQ);
+            return u < 6 * MQ && (x >> 2) < nq && va;
+        };
+        unsigned int off[NQ];
+        f32x4 sv[NQ];
+        unsigned int r4[NQ];
+        const RegionLut LU = uniform_lut(a);
 #pragma unroll
-    for (int m = 0; m < MV; ++m) {
-        const int x = t + TPF * m;
-        const int xc = x < a.nx ? x : a.nx - 1;
-        const unsigned int cell0 = (unsigned int)(r0c * a.nx + xc), cell1 = (unsigned int)(r1c * a.nx + xc);
-        idx0[m] = (c0 * (unsigned int)n + cell0) << 2;
-        idx1[m] = (c1 * (unsigned int)n + cell1) << 2;
-        g0[m] = a.region[cell0];
-        g1[m] = a.region[cell1];
-    }
-    // two batches (one per component) bound the loads in flight per thread
-    float sv[2 * MV];
-    {
-        float s0[MV], s1[MV];
-        stage_batch(a, rs, idx0, s0);
-        stage_batch(a, rs, idx1, s1);
+        for (int i = 0; i < NQ; ++i) {
+            int c, rr, x;
+            const bool in = place(tg + TG * i, c, rr, x);
+            const unsigned int cell = in ? (unsigned int)((ra + rr) * a.nx + x) : 0u;
+            off[i] = (cell + (in ? c : 0) * (unsigned int)n) << 2;
+            r4[i] = a.ureg < 0 ? regions4(a.region, cell) : 0u;
+        }
+        stage_quads(a, rs, off, sv);
+        if constexpr (!FUSED) {
+            if (a.ureg < 0) lut->store(lut_l, tid);
+            __syncthreads();
+        }
+        const float w = rs.dt * a_last;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            int c, rr, x;
+            if (!place(tg + TG * i, c, rr, x)) continue;
+            float* p = reinterpret_cast<float*>(gbuf + (c < 2 ? rr : 2) * SEQ + lds_pad(x)) + (c < 2 ? c : rr);
+            if constexpr (FUSED) sv[i] = fma4(w, f32x4{p[0], p[2], p[4], p[6]}, sv[i]);
+            if (a.sd.nk > 0 || FUSED) stq(a.ms, off[i], sv[i]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                p[2 * j] = (a.ureg < 0 ? lut_l[r4[i] >> (8 * j) & 255].a.x : LU.a.x) * sv[i][j];
+        }
+        __syncthreads();
 #pragma unroll
         for (int m = 0; m < MV; ++m) {
-            sv[m] = s0[m];
-            sv[MV + m] = s1[m];
+            const int x = t + TPF * m;
+            v[0][m] = x < a.nx && va ? buf[lds_pad(x)] : mkc(0.f, 0.f);
         }
-    }
-    if constexpr (FUSED) {
-        // the last term of the combine, k of the stage the x-inverse part of
-        // this workgroup just finished (after the barrier that published it)
-        const float w = rs.dt * a_last;
+    } else {
+        // slot 0: (x, y) of row a, slot 1: (x, y) of row b, slot 2: z of rows a and b
+        const int r0 = slot == 1 ? rb : ra;
+        const bool v0 = slot == 1 ? vb : va;
+        const int c0 = slot == 2 ? 2 : 0;
+        const int r1 = slot == 0 ? ra : rb;
+        const bool v1 = slot == 0 ? va : vb;
+        const int c1 = slot == 2 ? 2 : 1;
+        const int rr0 = slot == 1 ? 1 : 0, rr1 = slot == 0 ? 0 : 1;  // rows within the pair
+
+        // rows and columns past the grid are clamped for the loads and masked
+        // afterwards, so every load of the thread is issued before the first
+        // one is used
+        const int r0c = v0 ? r0 : 0, r1c = v1 ? r1 : 0;
+        unsigned int idx0[MV], idx1[MV];  // byte offsets into the [3][ncell] arrays
+        int g0[MV], g1[MV];
 #pragma unroll
         for (int m = 0; m < MV; ++m) {
             const int x = t + TPF * m;
             const int xc = x < a.nx ? x : a.nx - 1;
-            sv[m] += w * *k_slot<P, FULL>(gbuf, c0, rr0, xc, a.nx);
-            sv[MV + m] += w * *k_slot<P, FULL>(gbuf, c1, rr1, xc, a.nx);
+            const unsigned int cell0 = (unsigned int)(r0c * a.nx + xc), cell1 = (unsigned int)(r1c * a.nx + xc);
+            idx0[m] = (c0 * (unsigned int)n + cell0) << 2;
+            idx1[m] = (c1 * (unsigned int)n + cell1) << 2;
+            g0[m] = a.region[cell0];
+            g1[m] = a.region[cell1];
         }
-    } else {
-        lut->store(lut_l, tid);
-        __syncthreads();
-    }
+        // two batches (one per component) bound the loads in flight per thread
+        float sv[2 * MV];
+        {
+            float s0[MV], s1[MV];
+            stage_batch(a, rs, idx0, s0);
+            stage_batch(a, rs, idx1, s1);
 #pragma unroll
-    for (int m = 0; m < MV; ++m) {
-        const int x = t + TPF * m;
-        const bool in = x < a.nx;
-        if (a.sd.nk > 0 || FUSED) {
-            if (in && v0) sto(a.ms, idx0[m], sv[m]);
-            if (in && v1) sto(a.ms, idx1[m], sv[MV + m]);
+            for (int m = 0; m < MV; ++m) {
+                sv[m] = s0[m];
+                sv[MV + m] = s1[m];
+            }
         }
-        const float re = (in && v0) ? lut_l[g0[m]].a.x * sv[m] : 0.f;
-        const float im = (in && v1) ? lut_l[g1[m]].a.x * sv[MV + m] : 0.f;
-        v[0][m] = mkc(re, im);
+        if constexpr (FUSED) {
+            // the last term of the combine, k of the stage the x-inverse part of
+            // this workgroup just finished (after the barrier that published it)
+            const float w = rs.dt * a_last;
+#pragma unroll
+            for (int m = 0; m < MV; ++m) {
+                const int x = t + TPF * m;
+                const int xc = x < a.nx ? x : a.nx - 1;
+                sv[m] += w * *k_slot<P, FULL>(gbuf, c0, rr0, xc, a.nx);
+                sv[MV + m] += w * *k_slot<P, FULL>(gbuf, c1, rr1, xc, a.nx);
+            }
+        } else {
+            lut->store(lut_l, tid);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int m = 0; m < MV; ++m) {
+            const int x = t + TPF * m;
+            const bool in = x < a.nx;
+            if (a.sd.nk > 0 || FUSED) {
+                if (in && v0) sto(a.ms, idx0[m], sv[m]);
+                if (in && v1) sto(a.ms, idx1[m], sv[MV + m]);
+            }
+            const float re = (in && v0) ? lut_l[g0[m]].a.x * sv[m] : 0.f;
+            const float im = (in && v1) ? lut_l[g1[m]].a.x * sv[MV + m] : 0.f;
+            v[0][m] = mkc(re, im);
+        }
     }
     constexpr bool IW = TPF <= 64;  // a slot's threads lie in one wave
     // the other slots have read the finished stage's torque from this buffer
-    if constexpr (FUSED && IW) __syncthreads();
+    if constexpr (FUSED && IW && !Q4) __syncthreads();
     // x >= nx is zero padding (nx <= P/2) unless the axis is unpadded
     RegFft<P, TPF, 1, false, (P >= 2 && !FULL)>::run(v, buf, a.tw, a.twshift, t);
 
@@ -291,13 +376,25 @@ __device__ inline void xfwd_part(const FieldArgs& a, const Resolved& rs, cf* lds
         }
     }
     __syncthreads();
-    const Staged<P, XW> sc(tid);
+    if constexpr (Q4) {
+        const StagedPairs<P, XW> sc(tid);
 #pragma unroll
-    for (int i = 0; i < Staged<P, XW>::NIT; ++i) {
-        int li;
-        long long off;
-        sc.at(a, rbs, i, li, off);
-        if (off >= 0) a.spec[off] = lds[li];
+        for (int i = 0; i < StagedPairs<P, XW>::NIT; ++i) {
+            int li;
+            long long off;
+            sc.at(a, rbs, i, li, off);
+            if (off >= 0)
+                *reinterpret_cast<f32x4*>(a.spec + off) = *reinterpret_cast<const f32x4*>(lds + li);
+        }
+    } else {
+        const Staged<P, XW> sc(tid);
+#pragma unroll
+        for (int i = 0; i < Staged<P, XW>::NIT; ++i) {
+            int li;
+            long long off;
+            sc.at(a, rbs, i, li, off);
+            if (off >= 0) a.spec[off] = lds[li];
+        }
     }
 }
 
@@ -308,7 +405,7 @@ __device__ inline void xfwd_part(const FieldArgs& a, const Resolved& rs, cf* lds
 // once the staged spectrum is in LDS, before anything is written to global
 // memory, and the call returns false: the solver-state read behind the test
 // then overlaps the spectrum loads instead of preceding them.
-template <int P, bool FUSED, bool DMI = false, bool FULL = false, int XW = 0>
+template <int P, bool FUSED, bool DMI = false, bool FULL = false, int XW = 0, bool Q4 = false>
 __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds, const long long* rbs,
                                  RegionLut* lut_l, double* red, int blk, int tid) {
     constexpr int PPT = Cfg<P>::PPT, TPF = Cfg<P>::TPF, GI = XCfg<P, XW>::GI, NTH = XCfg<P, XW>::NTH;
@@ -319,24 +416,42 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
     cf* gbuf = lds + g * GL;
     cf* buf = gbuf + slot * SEQ;
 
-    XLut<P, XW> lut;
-    lut.load(a, tid);
     // read the half spectra of the row pairs in contiguous runs into
     // [kx][row][component]: every load of the thread first, then the LDS writes
-    const Staged<P, XW> sc(tid);
-    constexpr int NIT = Staged<P, XW>::NIT;
-    cf tmp[NIT];
-    int li[NIT];
+    XLut<P, XW> lut;
+    if constexpr (Q4) {
+        if (a.ureg < 0) lut.load(a, tid);
+        const StagedPairs<P, XW> sc(tid);
+        constexpr int NIT = StagedPairs<P, XW>::NIT;
+        f32x4 tmp[NIT];
+        int li[NIT];
 #pragma unroll
-    for (int i = 0; i < NIT; ++i) {
-        long long off;
-        sc.at(a, rbs, i, li[i], off);
-        tmp[i] = off >= 0 ? a.spec[off] : mkc(0.f, 0.f);
+        for (int i = 0; i < NIT; ++i) {
+            long long off;
+            sc.at(a, rbs, i, li[i], off);
+            tmp[i] = off >= 0 ? *reinterpret_cast<const f32x4*>(a.spec + off) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < NIT; ++i)
+            if (i < NIT - 1 || li[i] >= 0) *reinterpret_cast<f32x4*>(lds + li[i]) = tmp[i];
+        if (a.ureg < 0) lut.store(lut_l, tid);
+    } else {
+        lut.load(a, tid);
+        const Staged<P, XW> sc(tid);
+        constexpr int NIT = Staged<P, XW>::NIT;
+        cf tmp[NIT];
+        int li[NIT];
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) {
+            long long off;
+            sc.at(a, rbs, i, li[i], off);
+            tmp[i] = off >= 0 ? a.spec[off] : mkc(0.f, 0.f);
+        }
+#pragma unroll
+        for (int i = 0; i < NIT; ++i)
+            if (i < NIT - 1 || sc.kq0 + Staged<P, XW>::KS * i < Staged<P, XW>::GI * XCfg<P, XW>::KH) lds[li[i]] = tmp[i];
+        lut.store(lut_l, tid);
     }
-#pragma unroll
-    for (int i = 0; i < NIT; ++i)
-        if (i < NIT - 1 || sc.kq0 + Staged<P, XW>::KS * i < Staged<P, XW>::GI * XCfg<P, XW>::KH) lds[li[i]] = tmp[i];
-    lut.store(lut_l, tid);
     __syncthreads();
     if ((a.flags & EPI_CHECK_DONE) && rs.done) return false;
     // slot s = u + i w (slot 0: x, y of row a; slot 1: x, y of row b; slot 2: z of
@@ -387,12 +502,12 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
         const cf v01 = b3[(rr & 1) * SEQ + lds_pad(x)];
         const cf v2 = b3[2 * SEQ + lds_pad(x)];
         const int row = 2 * pair0 + rr;
-        const float3 tq = epilogue<DMI>(a, rs, lut_l, mp, (long long)row * a.nx + x, x, y, z,
+        const float3 tq = epilogue<DMI, Q4>(a, rs, lut_l, mp, (long long)row * a.nx + x, x, y, z,
                                    make_float3(v01.x, v01.y, (rr & 1) ? v2.y : v2.x), acc);
         if constexpr (FUSED) {
-            *k_slot<P, FULL>(b3, 0, rr & 1, x, a.nx) = tq.x;
-            *k_slot<P, FULL>(b3, 1, rr & 1, x, a.nx) = tq.y;
-            *k_slot<P, FULL>(b3, 2, rr & 1, x, a.nx) = tq.z;
+            *k_slot<P, FULL || Q4>(b3, 0, rr & 1, x, a.nx) = tq.x;
+            *k_slot<P, FULL || Q4>(b3, 1, rr & 1, x, a.nx) = tq.y;
+            *k_slot<P, FULL || Q4>(b3, 2, rr & 1, x, a.nx) = tq.z;
         }
     };
     constexpr int NROW = 2 * GI;

@@ -154,6 +154,15 @@ __device__ inline float3 stage_state(const FieldArgs& a, const Resolved& r, long
     return make_float3(stage_comp(a, r, cell), stage_comp(a, r, n + cell), stage_comp(a, r, 2 * n + cell));
 }
 
+// a grid's table entry when it has one region (uniform: scalar loads)
+__device__ inline RegionLut uniform_lut(const FieldArgs& a) {
+#if __HIP_DEVICE_COMPILE__
+    return *(const __attribute__((address_space(4))) RegionLut*)(a.lut + (a.ureg < 0 ? 0 : a.ureg));
+#else
+    return a.lut[0];
+#endif
+}
+
 // Exchange field at (x, y, z) from the state array mp.  A neighbour outside
 // the grid is replaced by the cell itself (the Neumann rule), which adds
 // c (m - m) = 0; so every neighbour is loaded without a branch.  Along a
@@ -161,10 +170,14 @@ __device__ inline float3 stage_state(const FieldArgs& a, const Resolved& r, long
 // neighbour slots have fixed positions (x-, x+, y-, y+, z-, z+) so the arrays
 // stay in registers; the y and z pairs are skipped (uniformly) for a single
 // layer along that axis.
+// ONE: where the whole grid lies in one region (a.ureg) every pair coefficient is
+// `self` and neither regions nor pair coefficients (a second, dependent trip of
+// loads) are read.  Without it the test is compiled out: wide workgroups hide
+// that trip, and lose 1 % (512^2 x 16 with 16 regions) by the test.
 // DMI = false compiles the DMI branch out (the hot x passes of grids without it).
-template <bool DMI = true>
+template <bool DMI = true, bool ONE = false>
 __device__ inline float3 exchange_at(const FieldArgs& a, const RegionLut* lut, const float* __restrict__ mp,
-                                     long long cell, int x, int y, int z, int r, float3 mc) {
+                                     long long cell, int x, int y, int z, int r, float3 mc, float self) {
     const long long n = a.ncell;
     const int sxy = a.nx * a.ny;
     const bool use_y = a.ny > 1, use_z = a.nz > 1;
@@ -188,7 +201,7 @@ __device__ inline float3 exchange_at(const FieldArgs& a, const RegionLut* lut, c
         const bool use = i < 2 || (i < 4 ? use_y : use_z);
         if (use) {
             const unsigned int q = c + (unsigned int)d[i];
-            rn[i] = a.region[q];
+            rn[i] = ONE && a.ureg >= 0 ? a.ureg : (int)a.region[q];
             mn[i] = ld3o(mp, n, q << 2);
         }
     }
@@ -196,7 +209,10 @@ __device__ inline float3 exchange_at(const FieldArgs& a, const RegionLut* lut, c
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         const bool use = i < 2 || (i < 4 ? use_y : use_z);
-        if (use) b = f3add(b, f3scale(a.ptab[pair_index(r, rn[i])] * id2[i / 2], f3sub(mn[i], mc)));
+        if (use) {
+            const float w = ONE && a.ureg >= 0 ? self : a.ptab[pair_index(r, rn[i])];
+            b = f3add(b, f3scale(w * id2[i / 2], f3sub(mn[i], mc)));
+        }
     }
     if (DMI && a.dmi) {
         // induced DMI (section "Dzyaloshinskii-Moriya interaction"):
@@ -254,14 +270,18 @@ __device__ inline void epi_init(EpiAcc& acc) {
 // Everything after the magnetostatic field for one cell.
 // lut: the region table (global memory, or a copy in LDS).  Returns the
 // torque (zero in non-magnetic cells; only meaningful with EPI_TORQUE).
-template <bool DMI = true>
+template <bool DMI = true, bool ONE = false>
 __device__ inline float3 epilogue(const FieldArgs& a, const Resolved& rs, const RegionLut* lut,
                                 const float* __restrict__ mp, long long cell, int x, int y, int z, float3 bd,
                                 EpiAcc& acc) {
     const int flags = a.flags;
     const unsigned int c4 = (unsigned int)cell << 2;
-    const int r = a.region[(unsigned int)cell];
-    const RegionLut L = lut[r];
+    const int r = ONE && a.ureg >= 0 ? a.ureg : (int)a.region[(unsigned int)cell];
+    RegionLut L;
+    if (ONE && a.ureg >= 0)
+        L = uniform_lut(a);
+    else
+        L = lut[r];
     const long long n = a.ncell;
     if (flags & EPI_BDEMAG) st3o(a.bdemag, n, c4, bd);
     float3 tq = make_float3(0.f, 0.f, 0.f);
@@ -271,7 +291,7 @@ __device__ inline float3 epilogue(const FieldArgs& a, const Resolved& rs, const 
         return tq;
     }
     const float3 m = ld3o(mp, n, c4);
-    const float3 bex = exchange_at<DMI>(a, lut, mp, cell, x, y, z, r, m);
+    const float3 bex = exchange_at<DMI, ONE>(a, lut, mp, cell, x, y, z, r, m, L.c.w);
     const float3 u = make_float3(L.b.x, L.b.y, L.b.z);
     const float um = f3dot(u, m);
     const float3 ban1 = f3scale(L.a.y * um, u);
@@ -334,6 +354,69 @@ __device__ inline float3 epilogue(const FieldArgs& a, const Resolved& rs, const 
     }
     return tq;
 }
+
+// ---- four cells at a time ---------------------------------------------------
+// The stage combine of the x passes takes four cells x ... x + 3 of a row and
+// component per thread with 16-byte loads and stores (x_quads): the address unit
+// takes 16 cycles for a wave's access whatever its width.  Products and sums
+// fuse only where written, so that every instance (tile shapes, ensembles) rounds
+// alike.
+#pragma clang fp contract(off)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline f32x4 ldq(const float* base, unsigned int off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(buffer_of(base), (int)off, 0, 0));
+}
+__device__ inline void stq(float* base, unsigned int off, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buffer_of(base), (int)off, 0, 0);
+}
+__device__ inline float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline f32x4 fma4(float s, f32x4 a, f32x4 b) {
+    return f32x4{fma1(s, a[0], b[0]), fma1(s, a[1], b[1]), fma1(s, a[2], b[2]), fma1(s, a[3], b[3])};
+}
+// regions of four adjacent cells, one per byte
+__device__ inline unsigned int regions4(const uint8_t* region, unsigned int cell) {
+    unsigned int r;
+    __builtin_memcpy(&r, region + cell, 4);
+    return r;
+}
+// Stage-state components of four adjacent cells at byte offset off:
+// m0 + dt sum_{j<NK} a_j k_j.
+template <int NK, int N>
+__device__ inline void stage_quads_nk(const FieldArgs& a, const Resolved& r, const unsigned int (&off)[N],
+                                      f32x4 (&out)[N]) {
+    f32x4 kv[N][NK > 0 ? NK : 1];
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = ldq(a.m0, off[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < NK; ++j) kv[i][j] = ldq(r.kin[j], off[i]);
+    if constexpr (NK > 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            f32x4 acc = a.sd.a[0] * kv[i][0];
+#pragma unroll
+            for (int j = 1; j < NK; ++j) acc = fma4(a.sd.a[j], kv[i][j], acc);
+            out[i] = fma4(r.dt, acc, out[i]);
+        }
+    }
+}
+template <int N>
+__device__ inline void stage_quads(const FieldArgs& a, const Resolved& r, const unsigned int (&off)[N],
+                                   f32x4 (&out)[N]) {
+    switch (a.sd.nk) {
+        case 0: stage_quads_nk<0>(a, r, off, out); break;
+        case 1: stage_quads_nk<1>(a, r, off, out); break;
+        case 2: stage_quads_nk<2>(a, r, off, out); break;
+        case 3: stage_quads_nk<3>(a, r, off, out); break;
+        case 4: stage_quads_nk<4>(a, r, off, out); break;
+        case 5: stage_quads_nk<5>(a, r, off, out); break;
+        default: stage_quads_nk<6>(a, r, off, out); break;
+    }
+}
+
+#pragma clang fp contract(fast)
 
 // Workgroup reductions ------------------------------------------------------
 __device__ inline float wave_max(float v) {

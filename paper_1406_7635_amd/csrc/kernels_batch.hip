@@ -131,6 +131,7 @@ __device__ inline FieldArgs member_field(const FieldArgs& b, const BMember& mb, 
     a.tau = b.tau ? b.tau + c3 : nullptr;
     a.partials = nullptr;
     a.cellvol = mb.cellvol;
+    a.ureg = -1;
     return a;
 }
 

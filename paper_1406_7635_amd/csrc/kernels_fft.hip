@@ -24,7 +24,8 @@ __device__ inline int x_tile_order(int t, const FieldArgs& a, int rows_per_tile)
 
 // FULL: x is a periodic axis transformed at its own length (P = nx).
 // W: workgroup width (XCfg): 0 wide, 1 narrow (grids with few rows).
-template <int P, bool FULL, int W>
+// Q4: wide spectrum copies and combines (x_quads).
+template <int P, bool FULL, int W, bool Q4>
 __global__ void __launch_bounds__((XCfg<P, W>::NTH)) k_xfwd(const FieldArgs a) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL;
     extern __shared__ cf lds[];
@@ -34,12 +35,12 @@ __global__ void __launch_bounds__((XCfg<P, W>::NTH)) k_xfwd(const FieldArgs a) {
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     row_bases<GI>(a, blk * GI, rbs, threadIdx.x);
     XLut<P, W> lut;
-    lut.load(a, threadIdx.x);
-    xfwd_part<P, false, FULL, W>(a, rs, lds, rbs, reinterpret_cast<RegionLut*>(lds + GI * GL), &lut, 0.f, blk,
+    if (!Q4 || a.ureg < 0) lut.load(a, threadIdx.x);
+    xfwd_part<P, false, FULL, W, Q4>(a, rs, lds, rbs, reinterpret_cast<RegionLut*>(lds + GI * GL), &lut, 0.f, blk,
                                  threadIdx.x);
 }
 
-template <int P, bool DMI, bool FULL, int W>
+template <int P, bool DMI, bool FULL, int W, bool Q4>
 __global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(P >= 4096 ? 4 : 6)))
 k_xinv(const FieldArgs a) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
@@ -52,7 +53,7 @@ k_xinv(const FieldArgs a) {
     // the solver state only now: its read overlaps the spectrum loads (the
     // finished-run test is inside, after them)
     const Resolved rs = resolve(a);
-    xinv_part<P, false, DMI, FULL, W>(a, rs, lds, rbs, reinterpret_cast<RegionLut*>(lds + GI * GL), red, blk,
+    xinv_part<P, false, DMI, FULL, W, Q4>(a, rs, lds, rbs, reinterpret_cast<RegionLut*>(lds + GI * GL), red, blk,
                                       threadIdx.x);
 }
 
@@ -62,7 +63,7 @@ k_xinv(const FieldArgs a) {
 // other workgroups still read m_s for the exchange field).
 // (FULL: every x holds data, so the combine keeps twice the loads in flight;
 // its register budget is that of four waves per SIMD instead of six)
-template <int P, bool DMI, bool FULL, int W>
+template <int P, bool DMI, bool FULL, int W, bool Q4>
 __global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL ? 4 : 6)))
 k_xrow(const FieldArgs ai, const FieldArgs af, float a_last) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
@@ -74,11 +75,11 @@ k_xrow(const FieldArgs ai, const FieldArgs af, float a_last) {
     __syncthreads();
     const Resolved rsi = resolve(ai);  // read overlaps the spectrum loads
     RegionLut* lut_l = reinterpret_cast<RegionLut*>(lds + GI * GL);
-    if (!xinv_part<P, true, DMI, FULL, W>(ai, rsi, lds, rbs, lut_l, red, blk, threadIdx.x)) return;
+    if (!xinv_part<P, true, DMI, FULL, W, Q4>(ai, rsi, lds, rbs, lut_l, red, blk, threadIdx.x)) return;
     __syncthreads();
     // the next stage's pointers only now (short live ranges across the first part)
     const Resolved rsf = resolve(af);
-    xfwd_part<P, true, FULL, W>(af, rsf, lds, rbs, lut_l, nullptr, a_last, blk, threadIdx.x);
+    xfwd_part<P, true, FULL, W, Q4>(af, rsf, lds, rbs, lut_l, nullptr, a_last, blk, threadIdx.x);
 }
 
 
@@ -142,10 +143,19 @@ template <int P, int W>
 static hipError_t xfwd_pw(const FieldArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const size_t lds = x_lds<P, W>();
     const dim3 g(x_blocks_w<P, W>(a.nrows)), b(XCfg<P, W>::NTH);
-    if (a.full_x)
-        hipExtLaunchKernelGGL((k_xfwd<P, true, W>), g, b, (uint32_t)lds, s, e0, e1, 0, a);
-    else
-        hipExtLaunchKernelGGL((k_xfwd<P, false, W>), g, b, (uint32_t)lds, s, e0, e1, 0, a);
+#define MM_XF(F, Q) hipExtLaunchKernelGGL((k_xfwd<P, F, W, Q>), g, b, (uint32_t)lds, s, e0, e1, 0, a)
+    if (x_quads(P, a.nx, a.ny, a.dmi != nullptr)) {
+        if (a.full_x)
+            MM_XF(true, P >= 8);
+        else
+            MM_XF(false, P >= 8);
+    } else {
+        if (a.full_x)
+            MM_XF(true, false);
+        else
+            MM_XF(false, false);
+    }
+#undef MM_XF
     return hipGetLastError();
 }
 template <int P>
@@ -158,18 +168,23 @@ static hipError_t xinv_pw(const FieldArgs& a, hipStream_t s, int* nb_out, hipEve
     const size_t lds = x_lds<P, W>();
     const int nb = x_blocks_w<P, W>(a.nrows);
     if (nb_out) *nb_out = nb;
-#define MM_XI(D, F) \
-    hipExtLaunchKernelGGL((k_xinv<P, D, F, W>), dim3(nb), dim3(XCfg<P, W>::NTH), (uint32_t)lds, s, e0, e1, 0, a)
+#define MM_XI(D, F, Q) \
+    hipExtLaunchKernelGGL((k_xinv<P, D, F, W, Q>), dim3(nb), dim3(XCfg<P, W>::NTH), (uint32_t)lds, s, e0, e1, 0, a)
     if (a.dmi) {
         if (a.full_x)
-            MM_XI(true, true);
+            MM_XI(true, true, false);
         else
-            MM_XI(true, false);
+            MM_XI(true, false, false);
+    } else if (W == 1 && x_quads(P, a.nx, a.ny, false)) {
+        if (a.full_x)
+            MM_XI(false, true, P >= 8 && W == 1);
+        else
+            MM_XI(false, false, P >= 8 && W == 1);
     } else {
         if (a.full_x)
-            MM_XI(false, true);
+            MM_XI(false, true, false);
         else
-            MM_XI(false, false);
+            MM_XI(false, false, false);
     }
 #undef MM_XI
     return hipGetLastError();
@@ -184,18 +199,23 @@ static hipError_t xrow_pw(const FieldArgs& ai, const FieldArgs& af, float a_last
                           hipEvent_t e1) {
     const size_t lds = x_lds<P, W>();
     const dim3 g(x_blocks_w<P, W>(ai.nrows)), b(XCfg<P, W>::NTH);
-#define MM_XR(D, F) \
-    hipExtLaunchKernelGGL((k_xrow<P, D, F, W>), g, b, (uint32_t)lds, s, e0, e1, 0, ai, af, a_last)
+#define MM_XR(D, F, Q) \
+    hipExtLaunchKernelGGL((k_xrow<P, D, F, W, Q>), g, b, (uint32_t)lds, s, e0, e1, 0, ai, af, a_last)
     if (ai.dmi) {
         if (ai.full_x)
-            MM_XR(true, true);
+            MM_XR(true, true, false);
         else
-            MM_XR(true, false);
+            MM_XR(true, false, false);
+    } else if (W == 1 && x_quads(P, ai.nx, ai.ny, false)) {
+        if (ai.full_x)
+            MM_XR(false, true, W == 1);
+        else
+            MM_XR(false, false, W == 1);
     } else {
         if (ai.full_x)
-            MM_XR(false, true);
+            MM_XR(false, true, false);
         else
-            MM_XR(false, false);
+            MM_XR(false, false, false);
     }
 #undef MM_XR
     return hipGetLastError();
@@ -266,20 +286,29 @@ static hipError_t allow_lds(const void* f, size_t bytes) {
     return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+template <int P, int W, bool F, bool Q>
+static hipError_t configure_xwf(void) {
+    constexpr size_t L = x_lds<P, W>();
+    hipError_t e = allow_lds<P>((const void*)k_xfwd<P, F, W, Q>, L);
+    if constexpr (!Q || W == 1) {
+        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, false, F, W, Q>, L);
+        if constexpr (P >= 8)
+            if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, false, F, W, Q>, L);
+    }
+    if constexpr (!Q) {
+        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, true, F, W, false>, L);
+        if constexpr (P >= 8)
+            if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, true, F, W, false>, L);
+    }
+    return e;
+}
 template <int P, int W>
 static hipError_t configure_xw(void) {
-    constexpr size_t L = x_lds<P, W>();
-    hipError_t e = allow_lds<P>((const void*)k_xfwd<P, false, W>, L);
-    if (e == hipSuccess) e = allow_lds<P>((const void*)k_xfwd<P, true, W>, L);
-    if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, false, false, W>, L);
-    if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, true, false, W>, L);
-    if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, false, true, W>, L);
-    if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, true, true, W>, L);
+    hipError_t e = configure_xwf<P, W, false, false>();
+    if (e == hipSuccess) e = configure_xwf<P, W, true, false>();
     if constexpr (P >= 8) {
-        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, false, false, W>, L);
-        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, true, false, W>, L);
-        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, false, true, W>, L);
-        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, true, true, W>, L);
+        if (e == hipSuccess) e = configure_xwf<P, W, false, true>();
+        if (e == hipSuccess) e = configure_xwf<P, W, true, true>();
     }
     return e;
 }

@@ -32,7 +32,10 @@ __global__ void k_prepare_tables(const mm_params* __restrict__ p, RegionLut* __r
                           (float)al);
         L.b = make_float4((float)p->anis_u[i][0], (float)p->anis_u[i][1], (float)p->anis_u[i][2],
                           (float)(-gamma / (1.0 + al * al)));
-        L.c = make_float4((float)p->bext[i][0], (float)p->bext[i][1], (float)p->bext[i][2], 0.f);
+        // the pair table's entry (i, i)
+        const double l = ms > 0.0 ? p->aex[i] / ms : 0.0;
+        const double self = l + l > 0.0 ? 2.0 * 1.0 * (2.0 * l * l / (l + l)) : 0.0;
+        L.c = make_float4((float)p->bext[i][0], (float)p->bext[i][1], (float)p->bext[i][2], (float)self);
         lut[i] = L;
     }
     if (i < NREG * NREG) {
@@ -52,6 +55,41 @@ __global__ void k_prepare_tables(const mm_params* __restrict__ p, RegionLut* __r
 hipError_t launch_prepare_tables(const double* params64, RegionLut* lut, float* ptab, hipStream_t s) {
     hipLaunchKernelGGL(k_prepare_tables, dim3((NREG * NREG + 255) / 256), dim3(256), 0, s,
                        reinterpret_cast<const mm_params*>(params64), lut, ptab);
+    return hipGetLastError();
+}
+
+// Smallest | largest << 8 of the regions of every chunk of the grid, a workgroup each.
+__global__ void __launch_bounds__(1024) k_region_range(const uint8_t* __restrict__ region, long long n, long long chunk,
+                                                       int* __restrict__ range) {
+    __shared__ int lo[16], hi[16];
+    const long long i0 = (long long)blockIdx.x * chunk, i1 = i0 + chunk < n ? i0 + chunk : n;
+    int l = 255, h = 0;
+    for (long long i = i0 + threadIdx.x; i < i1; i += 1024) {
+        const int r = region[i];
+        l = min(l, r);
+        h = max(h, r);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        l = min(l, __shfl_xor(l, o, 64));
+        h = max(h, __shfl_xor(h, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        lo[threadIdx.x >> 6] = l;
+        hi[threadIdx.x >> 6] = h;
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int w = 1; w < 16; ++w) {
+        l = min(l, lo[w]);
+        h = max(h, hi[w]);
+    }
+    range[blockIdx.x] = l | h << 8;
+}
+
+hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, int* count,
+                               hipStream_t s) {
+    *count = (int)((n + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_region_range, dim3(*count), dim3(1024), 0, s, region, n, chunk, range);
     return hipGetLastError();
 }
 

@@ -82,6 +82,7 @@ struct mm_ctx {
     void* arena = nullptr;
     size_t scratch_bytes = 0;
     uint8_t* region = nullptr;
+    int ureg = -1;  // every cell lies in this region (-1: more than one)
     double* params64 = nullptr;
     RegionLut* lut = nullptr;
     float* ptab = nullptr;
@@ -190,6 +191,7 @@ FieldArgs base_args(mm_ctx* c, const float* m0) {
     a.cub = c->cub_on ? c->cub : nullptr;
     a.dmi = c->dmi_on ? c->dmi : nullptr;
     a.full_x = c->full_x ? 1 : 0;
+    a.ureg = c->ureg;
     return a;
 }
 
@@ -871,8 +873,29 @@ int mm_create(mm_ctx** out, const mm_grid* g, const mm_params* p, const uint8_t*
         if (e == hipSuccess)
             e = launch_set_state(c->st, 0.0, 1e-14, INFINITY, 1e-5, 0.8, 0.0, 0.0, 4, 1, 1, 0, c->stream);
         if (e == hipSuccess) e = launch_set_therm_step(c->st, 0, c->stream);
+        // whether the grid has a single region: ranges of chunks of cells (into
+        // the idle energy partials, four doubles per 256 cells and at least four)
+        int* range = reinterpret_cast<int*>(c->partials);
+        std::vector<int> hrange;
+        int nch = 0;
+        if (e == hipSuccess) e = launch_region_range(c->region, c->ncell, 1 << 15, range, &nch, c->stream);
+        try {
+            hrange.resize((size_t)nch);
+        } catch (...) {
+            e = hipErrorOutOfMemory;
+        }
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(hrange.data(), range, (size_t)nch * sizeof(int), hipMemcpyDeviceToHost, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         st = map_err(e);
+        if (st == MM_OK) {
+            c->ureg = hrange[0] & 255;
+            for (int r : hrange)
+                if (r != (c->ureg | c->ureg << 8)) {
+                    c->ureg = -1;
+                    break;
+                }
+        }
     }
     if (st == MM_OK) {
         c->hparams = new (std::nothrow) mm_params(*p);

@@ -21,7 +21,7 @@ constexpr double GAMMA_DEFAULT = 1.7595e11;
 struct RegionLut {
     float4 a;  // msat, 2 Ku1/Msat, 4 Ku2/Msat, alpha
     float4 b;  // anisotropy axis u (x, y, z), -gamma/(1+alpha^2)
-    float4 c;  // B_ext (x, y, z), 0
+    float4 c;  // B_ext (x, y, z), exchange coefficient of the region with itself
 };
 
 // Solver state that lives on the device so steps need no host round trip.
@@ -101,6 +101,7 @@ struct FieldArgs {
     // induced DMI per region (null: none): (2 D/Msat, D/(2 A))
     const float2* dmi;
     int full_x;                   // x is periodic and transformed unpadded (px = nx)
+    int ureg;                     // every cell lies in this region; -1: more than one
 };
 
 struct ColArgs {
@@ -250,6 +251,10 @@ hipError_t launch_bset_state(DevState* st, int n, double t, double dt, double t_
 hipError_t launch_prepare_tables(const double* params64, RegionLut* lut, float* ptab,
                                  hipStream_t s);
 hipError_t launch_twiddles(cf* tw, int pt, hipStream_t s);
+// range[i] <- smallest | largest << 8 region of the i-th `chunk` of the n cells;
+// returns the number of chunks in *count
+hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, int* count,
+                               hipStream_t s);
 hipError_t launch_combine(const FieldArgs& a, hipStream_t s);
 // bd_in (optional): a magnetostatic field [3][ncell] to use instead of none
 hipError_t launch_local(const FieldArgs& a, hipStream_t s, int* nblocks_out, const float* bd_in = nullptr);
