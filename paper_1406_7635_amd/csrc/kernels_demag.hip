@@ -8,10 +8,10 @@
 //     axis) of f (diagonal) and g (off-diagonal) over the corner lattice;
 //   far: N_ij = -(V/4 pi) <(3 w_i w_j - |w|^2 delta_ij)/|w|^5>, the dipole
 //     tensor averaged over the triangular density of destination-minus-source
-//     offsets with Gauss-Legendre quadrature on each half axis; the number of
-//     points per half axis falls from 8 to 2 with distance (the paper's
-//     "number of integration points chosen by distance"), keeping the
-//     relative error near 1e-12 where Newell's cancellation would not.
+//     offsets with the Gauss rule of that density along each axis; the number of
+//     points per axis falls from 11 to 3 with distance (the paper's "number of
+//     integration points chosen by distance"), keeping the relative error near
+//     1e-12 where Newell's cancellation would not.
 // The octant is mirrored into the padded grid with the parities of each
 // component (xx, yy, zz even; xy odd in x, y; xz odd in x, z; yz odd in y, z;
 // every displacement with |i| >= nx is zero), scaled by -mu0/(px py pz),
@@ -25,24 +25,80 @@
 
 namespace mm {
 
-// Gauss-Legendre nodes/weights on [-1, 1] for n = 1..8, table offset n(n-1)/2.
-constexpr int GL_MAXN = 8;
-constexpr int GL_TABLE = GL_MAXN * (GL_MAXN + 1) / 2;
-struct GaussLegendre {
-    double x[GL_TABLE], w[GL_TABLE];
-    GaussLegendre() {
-        for (int n = 1; n <= GL_MAXN; ++n) {
-            const int off = n * (n - 1) / 2;
-            for (int i = 0; i < n; ++i) {
-                double t = cos(M_PI * (i + 0.75) / (n + 0.5)), dp = 1.0;
-                for (int it = 0; it < 100; ++it) {
-                    const double pn = legendre(n, t, dp), dt = pn / dp;
-                    t -= dt;
-                    if (fabs(dt) < 1e-16) break;
+// Gauss rules of the triangular density 1 - |t| on [-1, 1] with n = 1..11 points,
+// table offset n(n-1)/2.  Far from the source the dipole tensor is smooth across
+// the density's kink, so n points integrate what took n Gauss-Legendre points on
+// each half axis.  Largest relative error of the tensor, and points per cell, over
+// cells of aspect 1 to 40 at the nearest distance (cell diagonals) of each band:
+//   from 2.5: 11 points 9e-14, 1331 (8 per half axis: 2e-12, 4096)
+//   from 4:    8 points 3e-13,  512 (6: 7e-12, 1728)
+//   from 6:    6 points 5e-12,  216 (5: 1e-11, 1000)
+//   from 12:   5 points 5e-13,  125 (4: 2e-11,  512)
+//   from 24:   4 points 8e-13,   64 (4 until 50, then 3: 3e-12, 216)
+//   from 80:   3 points 9e-13,   27 (3, and 2 from 400: 9e-12, 64)
+constexpr int GT_MAXN = 11;
+constexpr int GT_TABLE = GT_MAXN * (GT_MAXN + 1) / 2;
+struct TriangleGauss {
+    double x[GT_TABLE], w[GT_TABLE];
+    TriangleGauss() {
+        // the density's moments by Gauss-Legendre points on [0, 1] (exact to
+        // degree 2 NL - 1; degree 2 GT_MAXN + 1 is needed), even part only: the
+        // orthonormal polynomials p_k alternate in parity
+        constexpr int NL = 12;
+        double s[NL], m[NL], beta[GT_MAXN + 1], pa[NL], pb[NL];
+        for (int i = 0; i < NL; ++i) {
+            double t = cos(M_PI * (i + 0.75) / (NL + 0.5)), dp = 1.0;
+            for (int it = 0; it < 100; ++it) {
+                const double pn = legendre(NL, t, dp), dt = pn / dp;
+                t -= dt;
+                if (fabs(dt) < 1e-16) break;
+            }
+            (void)legendre(NL, t, dp);
+            s[i] = 0.5 * (1.0 + t);
+            m[i] = 2.0 * (1.0 - s[i]) / ((1.0 - t * t) * dp * dp);  // both halves
+            pa[i] = 0.0;
+            pb[i] = 1.0;  // p_0: the density's integral is 1
+        }
+        // recurrence t p_k = beta_{k+1} p_{k+1} + beta_k p_{k-1}, orthogonalised on the points
+        beta[0] = 0.0;
+        for (int k = 0; k < GT_MAXN; ++k) {
+            double q[NL], n2 = 0.0;
+            for (int i = 0; i < NL; ++i) {
+                q[i] = s[i] * pb[i] - beta[k] * pa[i];
+                n2 += m[i] * q[i] * q[i];
+            }
+            beta[k + 1] = sqrt(n2);
+            for (int i = 0; i < NL; ++i) {
+                pa[i] = pb[i];
+                pb[i] = q[i] / beta[k + 1];
+            }
+        }
+        // nodes: the zeros of p_n, symmetric about 0; weights 1 / sum_{k<n} p_k^2
+        for (int n = 1; n <= GT_MAXN; ++n) {
+            double* xn = x + n * (n - 1) / 2;
+            double* wn = w + n * (n - 1) / 2;
+            int found = 0;
+            if (n & 1) xn[found++] = 0.0;
+            constexpr int SCAN = 512;
+            for (int c = 0; c < SCAN && found < n; ++c) {
+                double lo = (c + 0.5) / SCAN, hi = (c + 1.5) / SCAN, sum;
+                if (c == 0) lo = 0.25 / SCAN;
+                const double flo = value(beta, n, lo, sum);
+                if (flo * value(beta, n, hi, sum) > 0.0) continue;
+                for (int it = 0; it < 60; ++it) {
+                    const double mid = 0.5 * (lo + hi);
+                    if (flo * value(beta, n, mid, sum) > 0.0)
+                        lo = mid;
+                    else
+                        hi = mid;
                 }
-                (void)legendre(n, t, dp);
-                x[off + i] = t;
-                w[off + i] = 2.0 / ((1.0 - t * t) * dp * dp);
+                xn[found++] = 0.5 * (lo + hi);
+                xn[found++] = -0.5 * (lo + hi);
+            }
+            for (int i = 0; i < n; ++i) {
+                double sum;
+                (void)value(beta, n, xn[i], sum);
+                wn[i] = 1.0 / sum;
             }
         }
     }
@@ -55,6 +111,18 @@ struct GaussLegendre {
             p1 = p2;
         }
         dp = n * (t * p1 - p0) / (t * t - 1.0);
+        return p1;
+    }
+    // p_n(t); sum: sum_{k<n} p_k(t)^2
+    static double value(const double* beta, int n, double t, double& sum) {
+        double p0 = 0.0, p1 = 1.0;
+        sum = 0.0;
+        for (int k = 0; k < n; ++k) {
+            sum += p1 * p1;
+            const double p2 = (t * p1 - beta[k] * p0) / beta[k + 1];
+            p0 = p1;
+            p1 = p2;
+        }
         return p1;
     }
 };
@@ -87,32 +155,26 @@ __device__ inline double newell_g(double x, double y, double z) {
 // weight of corner offset o (0, 1, 2 for -1, 0, 1) along one axis
 __device__ inline double corner_weight(int o) { return o == 1 ? 2.0 : -1.0; }
 
-// Quadrature points per half axis; from RHO_WAVE on at most four.
+// Quadrature points per axis (TriangleGauss).
 constexpr double RHO_NEAR = 2.5, RHO_WAVE = 12.0;
 __device__ inline int far_order(double rho) {
-    if (rho < 4.0) return 8;
-    if (rho < 6.0) return 6;
-    if (rho < RHO_WAVE) return 5;
-    if (rho < 50.0) return 4;
-    if (rho < 400.0) return 3;
-    return 2;
+    if (rho < 4.0) return 11;
+    if (rho < 6.0) return 8;
+    if (rho < RHO_WAVE) return 6;
+    if (rho < 24.0) return 5;
+    if (rho < 80.0) return 4;
+    return 3;
 }
 
-// Nodes and weights of order n on both halves of the axis [-h, h] with density
-// (h - |s|)/h^2: 2 n entries from offset n (n - 1) of a table for n = 1 .. 8.
-constexpr int AXIS_TABLE = GL_MAXN * (GL_MAXN + 1);
+// Nodes and weights of every order along each axis, scaled to [-h, h].
 struct AxisTable {
-    double s[3][AXIS_TABLE], w[3][AXIS_TABLE];
+    double s[3][GT_TABLE], w[3][GT_TABLE];
 };
-__device__ inline void axis_table(AxisTable& t, const GaussLegendre& gl, const double (&cell)[3], int tid, int nth) {
-    for (int e = tid; e < 3 * AXIS_TABLE; e += nth) {
-        const int ax = e / AXIS_TABLE, r = e - ax * AXIS_TABLE;
-        int n = 1;
-        while (n * (n + 1) <= r) ++n;
-        const int i = r - n * (n - 1), g = n * (n - 1) / 2 + i % n;
-        const double h = cell[ax], s = 0.5 * h * (1.0 + gl.x[g]);
-        t.s[ax][r] = i < n ? s : -s;
-        t.w[ax][r] = 0.5 * h * gl.w[g] * (h - s) / (h * h);
+__device__ inline void axis_table(AxisTable& t, const TriangleGauss& gt, const double (&cell)[3], int tid, int nth) {
+    for (int e = tid; e < 3 * GT_TABLE; e += nth) {
+        const int ax = e / GT_TABLE, r = e - ax * GT_TABLE;
+        t.s[ax][r] = cell[ax] * gt.x[r];
+        t.w[ax][r] = gt.w[r];
     }
 }
 
@@ -120,10 +182,10 @@ __device__ inline void axis_table(AxisTable& t, const GaussLegendre& gl, const d
 // yy, zz, xy, xz, yz of u.  Along z only three sums are needed per point; the
 // trace part of the dipole tensor follows from the same sums.
 __device__ inline void dipole_line(double ux, double uy, double wab, double Z, const double* sz, const double* wz,
-                                   int n2, double (&acc)[6]) {
+                                   int np, double (&acc)[6]) {
     const double q = ux * ux + uy * uy;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int c = 0; c < n2; ++c) {
+    for (int c = 0; c < np; ++c) {
         const double uz = Z + sz[c];
         const double ir = rsqrt(q + uz * uz), ir2 = ir * ir;
         const double w = wz[c] * (ir2 * ir2 * ir), wu = w * uz;
@@ -152,13 +214,13 @@ __device__ inline void dipole_finish(const double (&acc)[6], double vol, double 
 }
 
 // Cells from RHO_WAVE cell diagonals on: a thread per cell, bound by FP64
-// arithmetic (216 or 512 points, about 25 operations each; the six products per
-// point of the plain sum took 60): 1 M cells 0.3 ms, 4 M cells 4.4 -> 1.05 ms.
+// arithmetic (27 to 125 points, about 25 operations each): 1 M cells (256 x 256
+// x 16) 298 us with 216 or 512 points of the half-axis rules, 67 us.
 __global__ void __launch_bounds__(256) k_tensor_far(int nx, int ny, int nz, double dx, double dy, double dz,
-                                                    const GaussLegendre gl, double* __restrict__ out) {
+                                                    const TriangleGauss gt, double* __restrict__ out) {
     __shared__ AxisTable tab;
     const double cell[3] = {dx, dy, dz};
-    axis_table(tab, gl, cell, threadIdx.x, 256);
+    axis_table(tab, gt, cell, threadIdx.x, 256);
     __syncthreads();
     const long long n = (long long)nx * ny * nz;
     const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -169,27 +231,27 @@ __global__ void __launch_bounds__(256) k_tensor_far(int nx, int ny, int nz, doub
     const double X = i * dx, Y = j * dy, Z = k * dz;
     const double rho = sqrt(X * X + Y * Y + Z * Z) / sqrt(dx * dx + dy * dy + dz * dz);
     if (rho < RHO_WAVE) return;
-    const int n2 = 2 * far_order(rho), off = n2 / 2 * (n2 / 2 - 1);
+    const int np = far_order(rho), off = np * (np - 1) / 2;
     double acc[6] = {0, 0, 0, 0, 0, 0}, t[6];
-    for (int a = 0; a < n2; ++a)
-        for (int b = 0; b < n2; ++b)
+    for (int a = 0; a < np; ++a)
+        for (int b = 0; b < np; ++b)
             dipole_line(X + tab.s[0][off + a], Y + tab.s[1][off + b], tab.w[0][off + a] * tab.w[1][off + b], Z,
-                        tab.s[2] + off, tab.w[2] + off, n2, acc);
+                        tab.s[2] + off, tab.w[2] + off, np, acc);
     dipole_finish(acc, dx * dy * dz, t);
     for (int c = 0; c < 6; ++c) out[c * n + id] = t[c];
 }
 
 // Cells nearer than RHO_WAVE, a wave each (grid: the box bx x by x bz that
-// holds them): their 1000 to 4096 quadrature points or 162 evaluations of
+// holds them): their 216 to 1331 quadrature points or 162 evaluations of
 // Newell's functions, spread over the lanes.  (In a thread they took 1.3 ms
 // whatever the grid, a chain the rest of the launch waited for.)
 __global__ void __launch_bounds__(256) k_tensor_near(int nx, int ny, int nz, int bx, int by, int bz, double dx,
-                                                     double dy, double dz, const GaussLegendre gl,
+                                                     double dy, double dz, const TriangleGauss gt,
                                                      double* __restrict__ out) {
     __shared__ AxisTable tab;
     __shared__ double val[4][162];
     const double cell[3] = {dx, dy, dz};
-    axis_table(tab, gl, cell, threadIdx.x, 256);
+    axis_table(tab, gt, cell, threadIdx.x, 256);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long cid = (long long)blockIdx.x * 4 + wave;
@@ -226,12 +288,12 @@ __global__ void __launch_bounds__(256) k_tensor_near(int nx, int ny, int nz, int
             t[c] = s / (4.0 * M_PI * dx * dy * dz);
         }
     } else {
-        const int n2 = 2 * far_order(rho), off = n2 / 2 * (n2 / 2 - 1);
+        const int np = far_order(rho), off = np * (np - 1) / 2;
         double acc[6] = {0, 0, 0, 0, 0, 0};
-        for (int p = lane; p < n2 * n2; p += 64) {
-            const int a = p / n2, b = p - a * n2;
+        for (int p = lane; p < np * np; p += 64) {
+            const int a = p / np, b = p - a * np;
             dipole_line(X + tab.s[0][off + a], Y + tab.s[1][off + b], tab.w[0][off + a] * tab.w[1][off + b], Z,
-                        tab.s[2] + off, tab.w[2] + off, n2, acc);
+                        tab.s[2] + off, tab.w[2] + off, np, acc);
         }
 #pragma unroll
         for (int c = 0; c < 6; ++c)
@@ -247,7 +309,7 @@ __global__ void __launch_bounds__(256) k_tensor_near(int nx, int ny, int nz, int
 
 hipError_t demag_tensor_octant(int nx, int ny, int nz, double dx, double dy, double dz, double* out,
                                hipStream_t s) {
-    static const GaussLegendre gl;
+    static const TriangleGauss gt;
     const long long n = (long long)nx * ny * nz;
     const double reach = RHO_WAVE * sqrt(dx * dx + dy * dy + dz * dz);
     // a cell of slack: both kernels test rho themselves
@@ -256,10 +318,10 @@ hipError_t demag_tensor_octant(int nx, int ny, int nz, double dx, double dy, dou
     const long long nb = (long long)bx * by * bz;
     const double cx = (nx - 1) * dx, cy = (ny - 1) * dy, cz = (nz - 1) * dz;
     hipLaunchKernelGGL(k_tensor_near, dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, s, nx, ny, nz, bx, by, bz, dx, dy,
-                       dz, gl, out);
+                       dz, gt, out);
     if (sqrt(cx * cx + cy * cy + cz * cz) > 0.999 * reach)
         hipLaunchKernelGGL(k_tensor_far, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, nx, ny, nz, dx, dy, dz,
-                           gl, out);
+                           gt, out);
     return hipGetLastError();
 }
 
