@@ -171,13 +171,13 @@ __device__ inline RegionLut uniform_lut(const FieldArgs& a) {
 // stay in registers; the y and z pairs are skipped (uniformly) for a single
 // layer along that axis.
 // ONE: where the whole grid lies in one region (a.ureg) every pair coefficient is
-// `self` and neither regions nor pair coefficients (a second, dependent trip of
+// `self`, every Msat is `msat`, and neither regions nor pair coefficients (a second, dependent trip of
 // loads) are read.  Without it the test is compiled out: wide workgroups hide
-// that trip, and lose 1 % (512^2 x 16 with 16 regions) by the test.
+// that trip, and lose 1 % (256 x 256 x 64 grains) by the test.
 // DMI = false compiles the DMI branch out (the hot x passes of grids without it).
 template <bool DMI = true, bool ONE = false>
 __device__ inline float3 exchange_at(const FieldArgs& a, const RegionLut* lut, const float* __restrict__ mp,
-                                     long long cell, int x, int y, int z, int r, float3 mc, float self) {
+                                     long long cell, int x, int y, int z, int r, float3 mc, float self, float msat) {
     const long long n = a.ncell;
     const int sxy = a.nx * a.ny;
     const bool use_y = a.ny > 1, use_z = a.nz > 1;
@@ -229,14 +229,14 @@ __device__ inline float3 exchange_at(const FieldArgs& a, const RegionLut* lut, c
         const float3 gy = make_float3(0.f, -dm.y * mc.z, dm.y * mc.y);
         const bool wx = a.pbc & 1, wy = a.pbc & 2;
         const bool geo[4] = {x > 0 || wx, x < a.nx - 1 || wx, y > 0 || wy, y < a.ny - 1 || wy};
-        const float cs = a.ptab[pair_index(r, r)];
+        const float cs = ONE && a.ureg >= 0 ? self : a.ptab[pair_index(r, r)];
         float3 v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool loaded = i < 2 || use_y;
             const int rr = loaded ? rn[i] : r;
             const float3 val = loaded ? mn[i] : mc;
-            const bool real = geo[i] && lut[rr].a.x > 0.f;
+            const bool real = geo[i] && (ONE && a.ureg >= 0 ? msat : lut[rr].a.x) > 0.f;
             const float3 g = i < 2 ? gx : gy;
             const float h = i < 2 ? hx : hy;
             const float3 ghost = f3add(mc, f3scale((i & 1) ? h : -h, g));
@@ -291,7 +291,7 @@ __device__ inline float3 epilogue(const FieldArgs& a, const Resolved& rs, const 
         return tq;
     }
     const float3 m = ld3o(mp, n, c4);
-    const float3 bex = exchange_at<DMI, ONE>(a, lut, mp, cell, x, y, z, r, m, L.c.w);
+    const float3 bex = exchange_at<DMI, ONE>(a, lut, mp, cell, x, y, z, r, m, L.c.w, L.a.x);
     const float3 u = make_float3(L.b.x, L.b.y, L.b.z);
     const float um = f3dot(u, m);
     const float3 ban1 = f3scale(L.a.y * um, u);

@@ -144,7 +144,7 @@ static hipError_t xfwd_pw(const FieldArgs& a, hipStream_t s, hipEvent_t e0, hipE
     const size_t lds = x_lds<P, W>();
     const dim3 g(x_blocks_w<P, W>(a.nrows)), b(XCfg<P, W>::NTH);
 #define MM_XF(F, Q) hipExtLaunchKernelGGL((k_xfwd<P, F, W, Q>), g, b, (uint32_t)lds, s, e0, e1, 0, a)
-    if (x_quads(P, a.nx, a.ny, a.dmi != nullptr)) {
+    if (x_quads(P, a.nx, a.ny)) {
         if (a.full_x)
             MM_XF(true, P >= 8);
         else
@@ -170,22 +170,22 @@ static hipError_t xinv_pw(const FieldArgs& a, hipStream_t s, int* nb_out, hipEve
     if (nb_out) *nb_out = nb;
 #define MM_XI(D, F, Q) \
     hipExtLaunchKernelGGL((k_xinv<P, D, F, W, Q>), dim3(nb), dim3(XCfg<P, W>::NTH), (uint32_t)lds, s, e0, e1, 0, a)
-    if (a.dmi) {
-        if (a.full_x)
-            MM_XI(true, true, false);
-        else
-            MM_XI(true, false, false);
-    } else if (W == 1 && x_quads(P, a.nx, a.ny, false)) {
-        if (a.full_x)
-            MM_XI(false, true, P >= 8 && W == 1);
-        else
-            MM_XI(false, false, P >= 8 && W == 1);
+#define MM_XID(Q)                                       \
+    if (a.dmi) {                                        \
+        if (a.full_x)                                   \
+            MM_XI(true, true, Q);                       \
+        else                                            \
+            MM_XI(true, false, Q);                      \
+    } else if (a.full_x)                                \
+        MM_XI(false, true, Q);                          \
+    else                                                \
+        MM_XI(false, false, Q)
+    if (W == 1 && x_quads(P, a.nx, a.ny)) {
+        MM_XID((P >= 8 && W == 1));
     } else {
-        if (a.full_x)
-            MM_XI(false, true, false);
-        else
-            MM_XI(false, false, false);
+        MM_XID(false);
     }
+#undef MM_XID
 #undef MM_XI
     return hipGetLastError();
 }
@@ -201,22 +201,22 @@ static hipError_t xrow_pw(const FieldArgs& ai, const FieldArgs& af, float a_last
     const dim3 g(x_blocks_w<P, W>(ai.nrows)), b(XCfg<P, W>::NTH);
 #define MM_XR(D, F, Q) \
     hipExtLaunchKernelGGL((k_xrow<P, D, F, W, Q>), g, b, (uint32_t)lds, s, e0, e1, 0, ai, af, a_last)
-    if (ai.dmi) {
-        if (ai.full_x)
-            MM_XR(true, true, false);
-        else
-            MM_XR(true, false, false);
-    } else if (W == 1 && x_quads(P, ai.nx, ai.ny, false)) {
-        if (ai.full_x)
-            MM_XR(false, true, W == 1);
-        else
-            MM_XR(false, false, W == 1);
+#define MM_XRD(Q)                                       \
+    if (ai.dmi) {                                       \
+        if (ai.full_x)                                  \
+            MM_XR(true, true, Q);                       \
+        else                                            \
+            MM_XR(true, false, Q);                      \
+    } else if (ai.full_x)                               \
+        MM_XR(false, true, Q);                          \
+    else                                                \
+        MM_XR(false, false, Q)
+    if (W == 1 && x_quads(P, ai.nx, ai.ny)) {
+        MM_XRD((W == 1));
     } else {
-        if (ai.full_x)
-            MM_XR(false, true, false);
-        else
-            MM_XR(false, false, false);
+        MM_XRD(false);
     }
+#undef MM_XRD
 #undef MM_XR
     return hipGetLastError();
 }
@@ -292,13 +292,11 @@ static hipError_t configure_xwf(void) {
     hipError_t e = allow_lds<P>((const void*)k_xfwd<P, F, W, Q>, L);
     if constexpr (!Q || W == 1) {
         if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, false, F, W, Q>, L);
-        if constexpr (P >= 8)
+        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, true, F, W, Q>, L);
+        if constexpr (P >= 8) {
             if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, false, F, W, Q>, L);
-    }
-    if constexpr (!Q) {
-        if (e == hipSuccess) e = allow_lds<P>((const void*)k_xinv<P, true, F, W, false>, L);
-        if constexpr (P >= 8)
-            if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, true, F, W, false>, L);
+            if (e == hipSuccess) e = allow_lds<P>((const void*)k_xrow<P, true, F, W, Q>, L);
+        }
     }
     return e;
 }

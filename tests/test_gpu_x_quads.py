@@ -22,11 +22,25 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("grid", [(4, 2, 1), (4, 3, 1), (8, 2, 2), (12, 6, 1), (16, 10, 3), (60, 34, 1), (62, 34, 1),
                                   (64, 35, 1), (128, 64, 1), (260, 20, 2), (1024, 4, 1), (1028, 6, 1)])
 def test_field_and_steps_match_oracle(gpu, grid, pbc, nregions):
+    check(grid, pbc, nregions, False)
+
+
+@pytest.mark.parametrize("nregions", [1, 3])
+@pytest.mark.parametrize("grid,pbc", [((12, 6, 1), (0, 0, 0)), ((16, 10, 3), (1, 0, 0)), ((60, 34, 1), (0, 1, 0)),
+                                      ((62, 34, 1), (0, 0, 0)), ((64, 64, 1), (1, 1, 0)), ((1028, 6, 1), (0, 0, 0))])
+def test_field_and_steps_with_dmi(gpu, grid, pbc, nregions):
+    check(grid, pbc, nregions, True)
+
+
+def check(grid, pbc, nregions, dmi):
     import torch
 
     case = synth.random_problem(grid, (2e-9, 2.5e-9, 3e-9), seed=sum(grid) + nregions, nregions=nregions,
                                 vacuum=nregions > 1)
-    log("x quads", grid, pbc, nregions)
+    if dmi:
+        case["params"]["dind"] = np.zeros(256)
+        case["params"]["dind"][:nregions] = [2e-3, -1e-3, 3e-3][:nregions]
+    log("x quads", grid, pbc, nregions, dmi)
     ctx = mm.Context(case["grid"], case["cell"], case["region"], case["params"], pbc=pbc)
     prob = ofields.Problem(case["grid"], case["cell"], case["region"], case["params"], pbc=pbc)
     m = torch.from_numpy(np.ascontiguousarray(case["m0"])).to("cuda:0")
