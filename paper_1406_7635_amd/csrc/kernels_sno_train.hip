@@ -150,9 +150,9 @@ __global__ void __launch_bounds__(LOSS_CHUNKS) k_tr_loss_final(const SnoTrainArg
     if (threadIdx.x == 0) *loss = l / a.batch;
 }
 
-// out[k] = sum_r part[r][k] (FP64 accumulation), k < K: a workgroup takes 32
+// out[k] = sum_r part[r][k] (FP64), k < K: a workgroup takes 32
 // columns, 32 threads each (a thread per column walking all rows took 0.18 ms)
-__global__ void __launch_bounds__(1024) k_tr_reduce(const float* __restrict__ part, int nrows, int K,
+__global__ void __launch_bounds__(1024) k_tr_reduce(const double* __restrict__ part, int nrows, int K,
                                                     float* __restrict__ out) {
     __shared__ double red[32][33];
     const int k = blockIdx.x * 32 + (threadIdx.x & 31), r0 = threadIdx.x >> 5;

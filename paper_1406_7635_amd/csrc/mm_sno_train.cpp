@@ -23,7 +23,7 @@ struct mm_sno_trainer {
     float4* ex = nullptr;   // kept-mode table of the x transforms
     float* act = nullptr;   // h[5], GELU'[4], dz[2], y
     float2* modes = nullptr;
-    float* part = nullptr;
+    double* part = nullptr;
     double* lpart = nullptr;
     float* scale = nullptr;
     double* loss = nullptr;
@@ -75,7 +75,7 @@ int mm_sno_train_create(mm_sno_trainer** out, int32_t nx, int32_t ny, int32_t ba
     if (e == hipSuccess) e = hipMalloc((void**)&t->act, (size_t)(11 * fld + 3LL * batch * n) * sizeof(float));
     // H[0..3], modes, modes2: 6 kept-mode arrays, then the line array
     if (e == hipSuccess) e = hipMalloc((void**)&t->modes, (size_t)(6 * kept + line) * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&t->part, sno_train_part(nx, ny, batch) * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc((void**)&t->part, sno_train_part(nx, ny, batch) * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&t->lpart, (size_t)batch * 64 * 2 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&t->scale, (size_t)batch * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void**)&t->loss, sizeof(double));

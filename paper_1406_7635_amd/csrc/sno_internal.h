@@ -66,13 +66,13 @@ struct SnoTrainBufs {
     float2* modes2;                // [B][32][256]
     float* y;                      // prediction [B][3][n]
     float* dz[2];                  // gradients with respect to a layer's pre-GELU values [B][32][n]
-    float* part;                   // per-workgroup weight sums [sno_train_blocks][1155]
+    double* part;                  // weight sums [workgroups of a row pass][up to 1155]
     double* lpart;                 // [B][64][2] loss partial sums
     float* scale;                  // [B] per-sample loss scale
     double* loss;                  // the batch loss
 };
 hipError_t configure_sno_train(int nx);
-// floats of the weight-sum workspace
+// doubles of the weight-sum workspace
 size_t sno_train_part(int nx, int ny, int batch);
 hipError_t sno_train_grad(const SnoTrainArgs& a, const SnoTrainBufs& s, const float* m, const float* t,
                           hipStream_t st);

@@ -76,6 +76,11 @@ constexpr int GPITCH = 36;                  // LDS pitch of the g rows (16-byte 
 constexpr int KLAYER = SNO_C * SNO_C + SNO_C;   // dW, db
 constexpr int KPROJ = 3 * SNO_C + 3;            // dQ, dq
 constexpr int KLIFT = 3 * SNO_C + SNO_C;        // dP, dp
+// Pixels of an FP32 weight sum before it goes to FP64 (a wave takes up to 64 of
+// a row).  Equal terms, where the rounding adds up, 512 x 512, batch 128 (8192
+// pixels a wave): 1.2e-4 of a component in one FP32 chain, 7e-6 in these; 256 x
+// 256, batch 16 (256 pixels a wave, one flush): 1548 us before, 1557 us.
+constexpr int SUM_PIXELS = 256;
 
 // The passes.  ROW_LIFT: h0 = P m + p.  ROW_LAYER: one layer, h' = GELU(z).
 // ROW_OUT: the last layer with the projection y = scale (Q h' + q).
@@ -105,7 +110,7 @@ struct RowArgs {
     float* y;                     // prediction [b][3][n] (written by ROW_OUT, read by ROW_BOUT)
     const float* t;               // target
     const float* sb;              // per-sample loss scale
-    float* part;                  // weight sums of the workgroup [gridDim.x][K]
+    double* part;                 // weight sums of the workgroup [gridDim.x][K]
 };
 
 // waves that share a row: a wave per 32-pixel tile, up to the workgroup's 8
@@ -222,6 +227,10 @@ k_sno_row(const RowArgs<WT> a) {
     float db = 0.f, dyq[2] = {0.f, 0.f};
 
     const int groups = (a.rows + rg - 1) / rg;
+    // row groups until the weight sums leave the FP32 accumulators
+    const int period = SUM_PIXELS / (32 * ((nt + wpr - 1) >> ws));
+    int held = 0;
+    bool first = true;
     for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
         const int row = grp * rg + (wave >> ws);
         const int row_b = row < a.rows ? row / ny : 0, row_y = row < a.rows ? row - row_b * ny : 0;
@@ -420,50 +429,58 @@ k_sno_row(const RowArgs<WT> a) {
                 a.line[(long long)r * 1024 + ok] = s;
             }
         }
-    }
-    if constexpr (WGRAD) {
-        // the workgroup's weight sums: its waves' accumulators, one after the other
-        constexpr int K = MODE == ROW_BLIFT ? KLIFT : (MODE == ROW_BOUT ? KLAYER + KPROJ : KLAYER);
-        float* part = a.part + (long long)blockIdx.x * K;
-        auto sum_waves = [&](int e) {  // element e of the waves' tiles
-            float s = trs[e];
-            for (int w = 1; w < ROW_WAVES; ++w) s += trs[w * 32 * TPITCH + e];
-            return s;
-        };
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 16; ++i) tr[drow(i, h) * TPITCH + l] = dw[i];
-        __syncthreads();
-        if constexpr (MODE == ROW_BLIFT) {
-            for (int e = tid; e < KLIFT; e += ROW_NTH) {
-                const int c = e < 3 * C ? e / 3 : e - 3 * C, j = e < 3 * C ? e - 3 * c : 3;
-                part[e] = sum_waves(c * TPITCH + j);
-            }
-        } else {
-            for (int e = tid; e < C * C; e += ROW_NTH) part[e] = sum_waves((e >> 5) * TPITCH + (e & 31));
+        if constexpr (WGRAD) {
+            if (++held < period && grp + (int)gridDim.x < groups) continue;
+            // the weight sums of these row groups, the workgroup's waves one
+            // after the other, onto its FP64 partials (an element always by the
+            // same thread)
+            constexpr int K = MODE == ROW_BLIFT ? KLIFT : (MODE == ROW_BOUT ? KLAYER + KPROJ : KLAYER);
+            double* part = a.part + (long long)blockIdx.x * K;
+            auto add = [&](int k, int e) {  // element e of the waves' tiles to partial k
+                double s = trs[e];
+                for (int w = 1; w < ROW_WAVES; ++w) s += trs[w * 32 * TPITCH + e];
+                part[k] = first ? s : part[k] + s;
+            };
             __syncthreads();
-            if (h == 0) tr[l] = db;
-            if constexpr (MODE == ROW_BOUT) {
-                if (h == 0) {
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) tr[(1 + j) * TPITCH + l] = dq[j];
-                }
-                // dq_j: sum of dy_j over the lanes (half 0: x, half 1: y; half 0 again: z)
-                float s0 = dyq[0], s1 = dyq[1];
-                for (int off = 16; off > 0; off >>= 1) {
-                    s0 += __shfl_xor(s0, off, 64);
-                    s1 += __shfl_xor(s1, off, 64);
-                }
-                if (l == 0) {
-                    tr[4 * TPITCH + h] = s0;
-                    if (h == 0) tr[4 * TPITCH + 2] = s1;
-                }
-            }
+            for (int i = 0; i < 16; ++i) tr[drow(i, h) * TPITCH + l] = dw[i];
             __syncthreads();
-            for (int e = C * C + tid; e < K; e += ROW_NTH) {
-                const int k = e - C * C;  // db, then dQ, then dq: rows of 32
-                part[e] = sum_waves((k >> 5) * TPITCH + (k & 31));
+            if constexpr (MODE == ROW_BLIFT) {
+                for (int e = tid; e < KLIFT; e += ROW_NTH) {
+                    const int c = e < 3 * C ? e / 3 : e - 3 * C, j = e < 3 * C ? e - 3 * c : 3;
+                    add(e, c * TPITCH + j);
+                }
+            } else {
+                for (int e = tid; e < C * C; e += ROW_NTH) add(e, (e >> 5) * TPITCH + (e & 31));
+                __syncthreads();
+                if (h == 0) tr[l] = db;
+                if constexpr (MODE == ROW_BOUT) {
+                    if (h == 0) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) tr[(1 + j) * TPITCH + l] = dq[j];
+                    }
+                    // dq_j: sum of dy_j over the lanes (half 0: x, half 1: y; half 0 again: z)
+                    float s0 = dyq[0], s1 = dyq[1];
+                    for (int off = 16; off > 0; off >>= 1) {
+                        s0 += __shfl_xor(s0, off, 64);
+                        s1 += __shfl_xor(s1, off, 64);
+                    }
+                    if (l == 0) {
+                        tr[4 * TPITCH + h] = s0;
+                        if (h == 0) tr[4 * TPITCH + 2] = s1;
+                    }
+                }
+                __syncthreads();
+                for (int e = C * C + tid; e < K; e += ROW_NTH) {
+                    const int k = e - C * C;  // db, then dQ, then dq: rows of 32
+                    add(e, (k >> 5) * TPITCH + (k & 31));
+                }
             }
+            dw = zero16();
+            dq = zero16();
+            db = dyq[0] = dyq[1] = 0.f;
+            held = 0;
+            first = false;
         }
     }
 }
