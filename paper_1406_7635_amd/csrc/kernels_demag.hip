@@ -155,6 +155,14 @@ __device__ inline double newell_g(double x, double y, double z) {
 // weight of corner offset o (0, 1, 2 for -1, 0, 1) along one axis
 __device__ inline double corner_weight(int o) { return o == 1 ? 2.0 : -1.0; }
 
+// Distance from the source in cell diagonals.  Nothing fuses here, so the near and
+// the far kernel get the same bits for a cell and exactly one of them writes it,
+// also where the distance is RHO_WAVE itself ((20, 4, 4) of cubic cells).
+__device__ inline double cell_distance(double X, double Y, double Z, const double (&cell)[3]) {
+#pragma clang fp contract(off)
+    return sqrt(X * X + Y * Y + Z * Z) / sqrt(cell[0] * cell[0] + cell[1] * cell[1] + cell[2] * cell[2]);
+}
+
 // Quadrature points per axis (TriangleGauss).
 constexpr double RHO_NEAR = 2.5, RHO_WAVE = 12.0;
 __device__ inline int far_order(double rho) {
@@ -229,7 +237,7 @@ __global__ void __launch_bounds__(256) k_tensor_far(int nx, int ny, int nz, doub
     const long long rest = id / nx;
     const int j = (int)(rest % ny), k = (int)(rest / ny);
     const double X = i * dx, Y = j * dy, Z = k * dz;
-    const double rho = sqrt(X * X + Y * Y + Z * Z) / sqrt(dx * dx + dy * dy + dz * dz);
+    const double rho = cell_distance(X, Y, Z, cell);
     if (rho < RHO_WAVE) return;
     const int np = far_order(rho), off = np * (np - 1) / 2;
     double acc[6] = {0, 0, 0, 0, 0, 0}, t[6];
@@ -260,7 +268,7 @@ __global__ void __launch_bounds__(256) k_tensor_near(int nx, int ny, int nz, int
     const long long rest = cid / bx;
     const int j = (int)(rest % by), k = (int)(rest / by);
     const double X = i * dx, Y = j * dy, Z = k * dz;
-    const double rho = sqrt(X * X + Y * Y + Z * Z) / sqrt(dx * dx + dy * dy + dz * dz);
+    const double rho = cell_distance(X, Y, Z, cell);
     if (rho >= RHO_WAVE) return;
     double t[6];
     if (rho < RHO_NEAR) {
