@@ -788,7 +788,7 @@ __device__ inline void col_body(const ColArgs& a, int blk, cf* lds, int tid) {
             const cf m0 = bufs[lds_pad(q)], m1 = bufs[SEQ + lds_pad(q)], m2 = bufs[2 * SEQ + lds_pad(q)];
             if (!packed) {
                 const float3 K = krow(kx);
-                v[0][m] = K.x * m0 + K.y * m1 + K.z * m2;
+                v[0][m] = crow3(K.x, m0, K.y, m1, K.z, m2);
             } else {
                 // Z = A0 + i AN with A0, AN real along y: A0^(k) = (Z(k) + conj Z(-k))/2,
                 // AN^(k) = (Z(k) - conj Z(-k))/(2i); both field columns stay real, so
@@ -801,8 +801,8 @@ __device__ inline void col_body(const ColArgs& a, int blk, cf* lds, int tid) {
                 const cf an0 = mkc(0.5f * d0.y, -0.5f * d0.x), an1 = mkc(0.5f * d1.y, -0.5f * d1.x),
                          an2 = mkc(0.5f * d2.y, -0.5f * d2.x);
                 const float3 K0 = krow(0), KN = krow(a.pack_col);
-                const cf b0 = K0.x * a00 + K0.y * a01 + K0.z * a02;
-                const cf bn = KN.x * an0 + KN.y * an1 + KN.z * an2;
+                const cf b0 = crow3(K0.x, a00, K0.y, a01, K0.z, a02);
+                const cf bn = crow3(KN.x, an0, KN.y, an1, KN.z, an2);
                 v[0][m] = mkc(b0.x - bn.y, b0.y + bn.x);
             }
         }
@@ -925,16 +925,16 @@ __device__ inline void yz_body(const ColArgs& a, int blk, cf* lds, int tid) {
                     const float* e = gk + (ad == 0 ? 0 : 4 + 6 * (ad - 1));
                     const float kxx = e[0], kyy = e[1], kzz = e[2], kxy = sy * e[3];
                     const cf x0 = X[0][zi], x1 = X[1][zi], x2 = X[2][zi];
-                    B0 = B0 + kxx * x0 + kxy * x1;
-                    B1 = B1 + kxy * x0 + kyy * x1;
-                    B2 = B2 + kzz * x2;
+                    B0 = cfma(kxy, x1, cfma(kxx, x0, B0));
+                    B1 = cfma(kyy, x1, cfma(kxy, x0, B1));
+                    B2 = cfma(kzz, x2, B2);
                     if (ad > 0) {
                         // i g: i (a + i b) = (-b, a)
                         const float sd = d > 0 ? 1.f : -1.f;
                         const float gxz = sd * e[4], gyz = sd * sy * e[5];
-                        B0 = B0 + gxz * mkc(-x2.y, x2.x);
-                        B1 = B1 + gyz * mkc(-x2.y, x2.x);
-                        B2 = B2 + gxz * mkc(-x0.y, x0.x) + gyz * mkc(-x1.y, x1.x);
+                        B0 = cfma(gxz, mkc(-x2.y, x2.x), B0);
+                        B1 = cfma(gyz, mkc(-x2.y, x2.x), B1);
+                        B2 = cfma(gyz, mkc(-x1.y, x1.x), cfma(gxz, mkc(-x0.y, x0.x), B2));
                     }
                 }
                 if (zo < nz) {
@@ -1384,8 +1384,8 @@ __device__ inline void col3_body(const ColArgs& a, int blk, cf* lds, int tid) {
             const float4 k4 = kg[m];
             const float kxy = fq ? -k4.w : k4.w;
             const cf mx = v[0][m], my = v[1][m];
-            v[0][m] = k4.x * mx + kxy * my;
-            v[1][m] = kxy * mx + k4.y * my;
+            v[0][m] = cfma(kxy, my, k4.x * mx);
+            v[1][m] = cfma(k4.y, my, kxy * mx);
             v[2][m] = k4.z * v[2][m];
         }
     } else {
@@ -1419,7 +1419,7 @@ __device__ inline void col3_body(const ColArgs& a, int blk, cf* lds, int tid) {
                 float4 kp, km;
                 kpm(q, kp, km);
                 const cf zr = cconj(buf[lds_pad((P - q) & (P - 1))]);
-                v[2][m] = kp.z * v[2][m] + km.z * zr;
+                v[2][m] = cfma(km.z, zr, kp.z * v[2][m]);
             }
         }
         __syncthreads();
@@ -1440,8 +1440,8 @@ __device__ inline void col3_body(const ColArgs& a, int blk, cf* lds, int tid) {
                 kpm(q, kp, km);
                 const cf xr = cconj(buf[lds_pad(qn)]), yr = cconj(reg2[lds_pad(qn)]);
                 const cf zx = v[0][m], zy = v[1][m];
-                v[0][m] = kp.x * zx + kp.w * zy + km.x * xr + km.w * yr;
-                v[1][m] = kp.w * zx + kp.y * zy + km.w * xr + km.y * yr;
+                v[0][m] = cfma(km.w, yr, crow3(kp.x, zx, kp.w, zy, km.x, xr));
+                v[1][m] = cfma(km.y, yr, crow3(kp.w, zx, kp.y, zy, km.w, xr));
             }
         } else {
             const float4* kc = kh + (long long)(valid ? c : 0) * KHP;
@@ -1452,8 +1452,8 @@ __device__ inline void col3_body(const ColArgs& a, int blk, cf* lds, int tid) {
                 const float4 k4 = kc[fq ? P - q : q];
                 const float kxy = fq ? -k4.w : k4.w;
                 const cf mx = v[0][m], my = v[1][m];
-                v[0][m] = k4.x * mx + kxy * my;
-                v[1][m] = kxy * mx + k4.y * my;
+                v[0][m] = cfma(kxy, my, k4.x * mx);
+                v[1][m] = cfma(k4.y, my, kxy * mx);
                 v[2][m] = k4.z * v[2][m];
             }
         }
