@@ -40,8 +40,13 @@ __global__ void __launch_bounds__((XCfg<P, W>::NTH)) k_xfwd(const FieldArgs a) {
                                  threadIdx.x);
 }
 
+// Register budget: that of six waves per SIMD; with DMI the four-cell form needs 88
+// registers (six waves leave 80: 24 B of scratch a lane) and runs in narrow
+// workgroups, whose launches give a SIMD fewer waves anyway.  Field of a 512^2
+// periodic film with DMI 29.8 -> 28.2 us, 128 x 128 x 4 open 23.6 -> 22.4 us.
 template <int P, bool DMI, bool FULL, int W, bool Q4>
-__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(P >= 4096 ? 4 : 6)))
+__global__ void __launch_bounds__((XCfg<P, W>::NTH))
+__attribute__((amdgpu_waves_per_eu(P >= 4096 ? 4 : (DMI && Q4 ? 5 : 6))))
 k_xinv(const FieldArgs a) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
     extern __shared__ cf lds[];
@@ -62,9 +67,12 @@ k_xinv(const FieldArgs a) {
 // with k_s from LDS as the last term, m_{s+1} to af.ms, a second buffer since
 // other workgroups still read m_s for the exchange field).
 // (FULL: every x holds data, so the combine keeps twice the loads in flight;
-// its register budget is that of four waves per SIMD instead of six)
+// its register budget is that of four waves per SIMD instead of six, and of
+// three in the four-cell form: 139 registers, where four waves leave 128 and
+// 60 B of scratch a lane.  RK45 attempt of periodic films: 256^2 157 -> 155 us,
+// 256 x 256 x 4 171 -> 169 us)
 template <int P, bool DMI, bool FULL, int W, bool Q4>
-__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL ? 4 : 6)))
+__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL ? (Q4 ? 3 : 4) : 6)))
 k_xrow(const FieldArgs ai, const FieldArgs af, float a_last) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
     extern __shared__ cf lds[];
@@ -95,8 +103,11 @@ __global__ void __launch_bounds__(YCfg<P>::NTH) k_ycol(const ColArgs a) {
     ycol_body<P, MODE>(a, xcd_remap(blockIdx.x, gridDim.x), lds, threadIdx.x);
 }
 
+// (1024 points need 140 registers, where four waves per SIMD leave 128 and 20 B of
+// scratch a lane: 100 x 100 x 512 field 919 -> 891 us, 32 x 32 x 300 71 -> 69 us)
 template <int P>
-__global__ void __launch_bounds__(ZCfg<P>::NTH) __attribute__((amdgpu_waves_per_eu(P >= 4096 ? 2 : 4)))
+__global__ void __launch_bounds__(ZCfg<P>::NTH)
+__attribute__((amdgpu_waves_per_eu(P >= 4096 ? 2 : (P == 1024 ? 3 : 4))))
 k_zconv(const ColArgs a) {
     extern __shared__ cf lds[];
     zconv_body<P>(a, xcd_remap(blockIdx.x, gridDim.x), lds, threadIdx.x);
