@@ -1,7 +1,8 @@
-"""The staged z convolution at its shortest lengths, 4 and 8 points (2 to 4
-layers with more rows than the one-pass y/z form takes), where a plane of a tile
-has more 16-byte chunks than the workgroup has threads, and with a single
-column per kx (one row of cells).
+"""The staged 3D column passes at the ends of their lengths.  z convolution: 4 and
+8 points (2 to 4 layers with more rows than the one-pass y/z form takes), where
+a plane of a tile has more 16-byte chunks than the workgroup has threads, and a
+single column per kx (one row of cells).  y transforms: 1, 4, 8, 16, 32 and 64
+points, where columns are shorter than a wave, and 1024 and 2048.
 
 Against the oracle with the tolerance of test_gpu_columns.py; an ensemble's
 member, which takes the per-component form, must equal the single grid bit for
@@ -14,7 +15,8 @@ from tests.gpu_helpers import log, make_pair, rel_inf, to_np
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("grid", [(40, 600, 2), (70, 600, 2), (40, 600, 3), (140, 300, 4), (600, 1, 150)])
+@pytest.mark.parametrize("grid", [(40, 600, 2), (70, 600, 2), (40, 600, 3), (140, 300, 4), (600, 1, 150),
+                                  (1000, 2, 70), (1000, 3, 70), (900, 7, 40), (600, 10, 30), (300, 20, 40)])
 def test_field_matches_oracle(gpu, grid):
     import numpy as np
 
