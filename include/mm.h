@@ -154,14 +154,14 @@ int mm_create(mm_ctx **out, const mm_grid *g, const mm_params *p, const uint8_t 
 /* Build the demagnetising kernel (section "Magnetostatic field", paragraph
  * "Magnetostatic kernel"): the cell-averaged tensor N(d) for every cell
  * displacement in FP64 on the GPU -- Newell's closed form near the origin,
- * Gauss quadrature of the dipole tensor far away -- mirrored into the
- * padded grid using its symmetries, Fourier transformed in FP64, scaled by
+ * Gauss quadrature of the dipole tensor far away -- Fourier transformed in
+ * FP64 over the padded grid, which its mirror symmetries fill, scaled by
  * -mu0 / (px py pz) and truncated to FP32.  Only the non-redundant octant of
  * the real spectrum is kept (4 components in 2D, 6 in 3D).  With periodic
  * axes the tensor is evaluated over the whole image window (0 .. n P - 1 cells
  * along such an axis) and each box displacement takes the sum over its
  * images (its negative-displacement images by the tensor's parity) before
- * the mirror fill.  Its FP64 temporaries take the context's idle buffers; what
+ * the transform.  Its FP64 temporaries take the context's idle buffers; what
  * does not fit them is allocated and freed inside the call.  Synchronous. */
 int mm_demag_kernel_init(mm_ctx *c);
 

@@ -14,7 +14,9 @@ namespace mm {
 
 // No implicit contraction in this file: where a product and a sum fuse is
 // written out, so every instance of a transform (tile shapes, components per
-// thread, single grids and ensembles) rounds alike.
+// thread, single grids and ensembles) rounds alike.  That holds for the operators
+// below wherever they are used: a sum of products of a caller takes cfma and
+// crow3, or it rounds twice a term.
 #pragma clang fp contract(off)
 
 struct alignas(8) cf {

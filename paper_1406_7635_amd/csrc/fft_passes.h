@@ -150,8 +150,8 @@ struct StagedPairs {
 // the narrow one (64^2 film: fused 12.1 -> 10.9 us, inverse 10.6 -> 9.7 us), while
 // wide workgroups hide the accesses behind each other and lose the free half of
 // the slot buffers (fused: 1024^2 film 38.4 -> 38.2 us, 256 x 256 x 64 grains
-// 182 -> 186 us).  With DMI (512^2 periodic film): fused 19.7 -> 18.9 us, forward
-// 9.4 -> 8.6 us.  Rows are whole groups of four cells and pairs of rows;
+// 182 -> 186 us).  With DMI (512^2 periodic film): fused 19.7 -> 18.7 us, inverse
+// 19.9 -> 18.9 us, forward 9.4 -> 8.6 us.  Rows are whole groups of four cells and pairs of rows;
 // nx = 4 pads to 8, and shorter lengths (periodic rows) keep the other form.
 inline bool x_quads(int px, int nx, int ny) { return px >= 8 && nx % 4 == 0 && ny % 2 == 0; }
 

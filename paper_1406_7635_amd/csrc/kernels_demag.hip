@@ -340,7 +340,7 @@ hipError_t demag_tensor_octant(int nx, int ny, int nz, double dx, double dy, dou
 // of a periodic axis; a non-periodic axis keeps d = i.  The window tensor is
 // stored for d >= 0 (lengths wx, wy, wz); a negative d takes the parity of the
 // component along that axis.  With these sums in place of the octant, the
-// mirror fill below gives the displacement -d the entry of the box
+// mirrored entries (next section) give the displacement -d the entry of the box
 // displacement n - d (the sums satisfy S(n - d) = parity S(d)), so the padded
 // linear convolution becomes the cyclic one along the periodic axes.
 __global__ void __launch_bounds__(256) k_fold_images(int nx, int ny, int nz, int wx, int wy, int wz, int qx,
@@ -402,7 +402,10 @@ hipError_t demag_fold_images(int nx, int ny, int nz, const int* w, const int* pb
 // Why products instead of transforms: the octant has an eighth of the padded
 // points, and n x (p/2 + 1) tables on the FP64 matrix cores need no exchange,
 // no twiddles and no second pass over memory per axis.  One 256 x 256 x 16
-// kernel: mirror fill, 18 complex transforms and extraction 4.8 ms -> 0.34 ms.
+// kernel: mirror fill, 18 complex transforms and extraction 4.8 ms -> 0.34 ms.  The
+// work per point grows with the axis, so long axes gain least: the whole
+// construction, tensor included, of 2048 x 2048 cells 7.95 -> 4.61 ms, of
+// 2048 x 1 x 1 1.45 -> 0.56 ms, of 128 x 128 x 128 11.5 -> 0.56 ms.
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 

@@ -88,7 +88,7 @@ hipError_t sno_run(const mm_sno* s, const float* m, float* out, hipStream_t stre
 void sno_grid(const mm_sno* s, int* nx, int* ny);
 // the whole forward pass: m [3][n] -> out [3][n]
 hipError_t sno_forward(const SnoArgs& a, const float* m, float* out, hipStream_t s);
-// raise the LDS limit of the row passes (nx <= 512: 106 KB)
+// raise the LDS limit of the row passes (nx <= 512: 108 KiB)
 hipError_t configure_sno(int nx);
 
 }  // namespace mm

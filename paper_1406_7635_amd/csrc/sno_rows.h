@@ -19,7 +19,7 @@
 // kernel per product (x transform, GELU backward with its weight sums on the
 // vector units, pointwise part) every activation was read two or three times
 // and the sums over pixels took 0.83 ms a layer.  256 x 256, batch 16: loss and
-// gradient 7.4 -> 1.54 ms; one 256 x 256 prediction 244 -> 90 us.
+// gradient 7.4 -> 1.55 ms; one 256 x 256 prediction 244 -> 90 us.
 //
 // Operand layout of the instruction (wave of 64, h = lane / 32, l = lane % 32):
 // A[m = l][k = h], B[k = h][n = l], result register i = D[m = drow(i, h)][n = l].

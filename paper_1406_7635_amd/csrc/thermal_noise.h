@@ -55,7 +55,8 @@ __device__ inline float boxmuller_radius(float u) {
 }
 
 // sin and cos of 2 pi u for u in [0, 1]: u = n/4 + f exactly, |f| <= 1/8; minimax
-// polynomials in f^2 (5e-12 and 6e-11 of the value), 2 pi in two parts.
+// polynomials in f^2, 2 pi in two parts.  With the coefficients rounded to FP32 they
+// are within 1.9e-9 (sine) and 1.1e-8 (cosine) of the value.
 __device__ inline void sincos_turns(float u, float& sn, float& cs) {
     const float n = __builtin_rintf(4.f * u);
     const float f = __builtin_fmaf(n, -0.25f, u), z = f * f;
