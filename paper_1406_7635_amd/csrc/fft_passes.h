@@ -155,6 +155,15 @@ struct StagedPairs {
 // nx = 4 pads to 8, and shorter lengths (periodic rows) keep the other form.
 inline bool x_quads(int px, int nx, int ny) { return px >= 8 && nx % 4 == 0 && ny % 2 == 0; }
 
+// Whether the inverse pass has the one-region form of the epilogue (ONE): with
+// DMI it needs 88 registers, which leave five waves per SIMD instead of six.  The
+// workgroups of three waves lose nothing by that (their LDS admits six to a CU) and
+// gain from the reads left out (field of 512^2 periodic cells 29.6 -> 28.4 us); of
+// the six-wave ones of 1024 points only two instead of three would share a CU (300 x
+// 1500 cells: 67.8 against 65.1 us).
+template <int P, bool DMI, int W, bool Q4>
+constexpr bool x_one() { return Q4 && (!DMI || XCfg<P, W>::NTH <= 192); }
+
 // ---------------------------------------------------------------------------
 // x passes.  Both stage the region table in LDS after the row-pair area.
 template <int P, int W = 0>
@@ -420,8 +429,9 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
     // read the half spectra of the row pairs in contiguous runs into
     // [kx][row][component]: every load of the thread first, then the LDS writes
     XLut<P, XW> lut;
+    constexpr bool ONE = FUSED ? Q4 : x_one<P, DMI, XW, Q4>();
     if constexpr (Q4) {
-        if (a.ureg < 0) lut.load(a, tid);
+        if (!ONE || a.ureg < 0) lut.load(a, tid);
         const StagedPairs<P, XW> sc(tid);
         constexpr int NIT = StagedPairs<P, XW>::NIT;
         f32x4 tmp[NIT];
@@ -435,7 +445,7 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
 #pragma unroll
         for (int i = 0; i < NIT; ++i)
             if (i < NIT - 1 || li[i] >= 0) *reinterpret_cast<f32x4*>(lds + li[i]) = tmp[i];
-        if (a.ureg < 0) lut.store(lut_l, tid);
+        if (!ONE || a.ureg < 0) lut.store(lut_l, tid);
     } else {
         lut.load(a, tid);
         const Staged<P, XW> sc(tid);
@@ -503,7 +513,7 @@ __device__ inline bool xinv_part(const FieldArgs& a, const Resolved& rs, cf* lds
         const cf v01 = b3[(rr & 1) * SEQ + lds_pad(x)];
         const cf v2 = b3[2 * SEQ + lds_pad(x)];
         const int row = 2 * pair0 + rr;
-        const float3 tq = epilogue<DMI, Q4>(a, rs, lut_l, mp, (long long)row * a.nx + x, x, y, z,
+        const float3 tq = epilogue<DMI, ONE>(a, rs, lut_l, mp, (long long)row * a.nx + x, x, y, z,
                                    make_float3(v01.x, v01.y, (rr & 1) ? v2.y : v2.x), acc);
         if constexpr (FUSED) {
             *k_slot<P, FULL || Q4>(b3, 0, rr & 1, x, a.nx) = tq.x;

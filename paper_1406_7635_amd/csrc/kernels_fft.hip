@@ -25,8 +25,12 @@ __device__ inline int x_tile_order(int t, const FieldArgs& a, int rows_per_tile)
 // FULL: x is a periodic axis transformed at its own length (P = nx).
 // W: workgroup width (XCfg): 0 wide, 1 narrow (grids with few rows).
 // Q4: wide spectrum copies and combines (x_quads).
+// Register budget of the FULL forms: that of four waves per SIMD, or workgroups of
+// six waves (1024 points) share a CU less well (field of 1024 x 1024 periodic cells
+// 49.4 -> 46.1 us).
 template <int P, bool FULL, int W, bool Q4>
-__global__ void __launch_bounds__((XCfg<P, W>::NTH)) k_xfwd(const FieldArgs a) {
+__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL && P < 4096 ? 4 : 1)))
+k_xfwd(const FieldArgs a) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL;
     extern __shared__ cf lds[];
     __shared__ long long rbs[2 * GI];
@@ -40,13 +44,11 @@ __global__ void __launch_bounds__((XCfg<P, W>::NTH)) k_xfwd(const FieldArgs a) {
                                  threadIdx.x);
 }
 
-// Register budget: that of six waves per SIMD; with DMI the four-cell form needs 88
-// registers (six waves leave 80: 24 B of scratch a lane) and runs in narrow
-// workgroups, whose launches give a SIMD fewer waves anyway.  Field of a 512^2
-// periodic film with DMI 29.8 -> 28.2 us, 128 x 128 x 4 open 23.6 -> 22.4 us.
+// Register budget: that of six waves per SIMD, of five where the DMI form has the
+// one-region epilogue (x_one).
 template <int P, bool DMI, bool FULL, int W, bool Q4>
 __global__ void __launch_bounds__((XCfg<P, W>::NTH))
-__attribute__((amdgpu_waves_per_eu(P >= 4096 ? 4 : (DMI && Q4 ? 5 : 6))))
+__attribute__((amdgpu_waves_per_eu(P >= 4096 ? 4 : (DMI && x_one<P, DMI, W, Q4>() ? 5 : 6))))
 k_xinv(const FieldArgs a) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
     extern __shared__ cf lds[];
@@ -67,12 +69,9 @@ k_xinv(const FieldArgs a) {
 // with k_s from LDS as the last term, m_{s+1} to af.ms, a second buffer since
 // other workgroups still read m_s for the exchange field).
 // (FULL: every x holds data, so the combine keeps twice the loads in flight;
-// its register budget is that of four waves per SIMD instead of six, and of
-// three in the four-cell form: 139 registers, where four waves leave 128 and
-// 60 B of scratch a lane.  RK45 attempt of periodic films: 256^2 157 -> 155 us,
-// 256 x 256 x 4 171 -> 169 us)
+// its register budget is that of four waves per SIMD instead of six)
 template <int P, bool DMI, bool FULL, int W, bool Q4>
-__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL ? (Q4 ? 3 : 4) : 6)))
+__global__ void __launch_bounds__((XCfg<P, W>::NTH)) __attribute__((amdgpu_waves_per_eu(FULL ? 4 : 6)))
 k_xrow(const FieldArgs ai, const FieldArgs af, float a_last) {
     constexpr int GI = XCfg<P, W>::GI, GL = XCfg<P, W>::GL, NTH = XCfg<P, W>::NTH;
     extern __shared__ cf lds[];
