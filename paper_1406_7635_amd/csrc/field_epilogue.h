@@ -382,31 +382,42 @@ __device__ inline unsigned int regions4(const uint8_t* region, unsigned int cell
 }
 // Stage-state components of four adjacent cells at byte offset off:
 // m0 + dt sum_{j<NK} a_j k_j.
+// Loads in flight: at most 20 (80 registers), half of the cells after the other
+// half where more are needed.  No tableau's x pass combines more than four
+// derivatives, but the register count of a kernel is that of its largest case: with
+// 28 loads the fused pass of unpadded rows had 60 B of scratch a lane, or one
+// wave per SIMD less (1024 x 1024 periodic film, RK45 attempt 309 -> 346 us).
 template <int NK, int N>
 __device__ inline void stage_quads_nk(const FieldArgs& a, const Resolved& r, const unsigned int (&off)[N],
                                       f32x4 (&out)[N]) {
-    // Loads in flight: at most 20 (80 registers), a batch of the cells after the
-    // other where more are needed.  No tableau's x pass combines more than four
-    // derivatives, but the register count of a kernel is that of its largest case: with
-    // 28 loads the fused pass of unpadded rows had 60 B of scratch a lane, or one
-    // wave per SIMD less (1024 x 1024 periodic film, RK45 attempt 309 -> 346 us).
-    constexpr int B = N * (NK + 1) > 20 ? N / 2 : N;
+    if constexpr (N * (NK + 1) > 20) {
+        constexpr int H = N / 2;
+        static_assert(2 * H == N, "two halves");
 #pragma unroll
-    for (int i0 = 0; i0 < N; i0 += B) {
-        f32x4 kv[B][NK > 0 ? NK : 1];
+        for (int h = 0; h < 2; ++h) {
+            unsigned int o[H];
+            f32x4 v[H];
 #pragma unroll
-        for (int i = 0; i < B; ++i) out[i0 + i] = ldq(a.m0, off[i0 + i]);
+            for (int i = 0; i < H; ++i) o[i] = off[h * H + i];
+            stage_quads_nk<NK, H>(a, r, o, v);
 #pragma unroll
-        for (int i = 0; i < B; ++i)
+            for (int i = 0; i < H; ++i) out[h * H + i] = v[i];
+        }
+    } else {
+        f32x4 kv[N][NK > 0 ? NK : 1];
 #pragma unroll
-            for (int j = 0; j < NK; ++j) kv[i][j] = ldq(r.kin[j], off[i0 + i]);
+        for (int i = 0; i < N; ++i) out[i] = ldq(a.m0, off[i]);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j < NK; ++j) kv[i][j] = ldq(r.kin[j], off[i]);
         if constexpr (NK > 0) {
 #pragma unroll
-            for (int i = 0; i < B; ++i) {
+            for (int i = 0; i < N; ++i) {
                 f32x4 acc = a.sd.a[0] * kv[i][0];
 #pragma unroll
                 for (int j = 1; j < NK; ++j) acc = fma4(a.sd.a[j], kv[i][j], acc);
-                out[i0 + i] = fma4(r.dt, acc, out[i0 + i]);
+                out[i] = fma4(r.dt, acc, out[i]);
             }
         }
     }
