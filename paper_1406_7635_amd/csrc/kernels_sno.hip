@@ -84,7 +84,7 @@ hipError_t sno_forward(const SnoArgs& a, const float* m, float* out, hipStream_t
     r.ny = a.ny;
     r.n = a.n;
     r.rows = a.ny;
-    r.wshift = row_wave_shift(a.nx);
+    r.wshift = row_wave_shift(a.nx, r.rows);
     r.line = a.line;
     r.ex = a.ex;
     r.twy = a.twy;

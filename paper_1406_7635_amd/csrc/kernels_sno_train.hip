@@ -199,7 +199,8 @@ hipError_t configure_sno_train(int nx) {
 }
 
 size_t sno_train_part(int nx, int ny, int batch) {
-    return (size_t)row_blocks((long long)batch * ny, row_wave_shift(nx)) * (KLAYER + KPROJ);
+    const long long rows = (long long)batch * ny;
+    return (size_t)row_blocks(rows, row_wave_shift(nx, rows)) * (KLAYER + KPROJ);
 }
 
 // forward pass with the activations kept, loss, backward pass into a.g
@@ -211,7 +212,7 @@ hipError_t sno_train_grad(const SnoTrainArgs& a, const SnoTrainBufs& s, const fl
     r.ny = a.ny;
     r.n = a.n;
     r.rows = a.batch * a.ny;
-    r.wshift = row_wave_shift(a.nx);
+    r.wshift = row_wave_shift(a.nx, r.rows);
     r.line = s.line;
     r.ex = a.ex;
     r.twy = a.twy;

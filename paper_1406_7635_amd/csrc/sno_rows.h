@@ -113,11 +113,16 @@ struct RowArgs {
     double* part;                 // weight sums of the workgroup [gridDim.x][K]
 };
 
-// waves that share a row: a wave per 32-pixel tile, up to the workgroup's 8
-inline int row_wave_shift(int nx) {
+// Waves that share a row: a wave per 32-pixel tile, up to the workgroup's 8, and
+// more (some then without a tile) where the rows would not give each of the 256 CUs
+// a workgroup: the rows of a workgroup form their g one after the other.  One
+// prediction with a wave per tile and with this rule: 32 x 16 157, 69 us; 64 x 64 113,
+// 70 us; 64 x 512 134, 108 us.
+inline int row_wave_shift(int nx, long long rows) {
     const int tiles = (nx + 31) / 32;
     int s = 0;
     while ((1 << s) < tiles && s < 3) ++s;
+    while (s < 3 && rows < 256LL * (ROW_WAVES >> s)) ++s;
     return s;
 }
 inline size_t row_lds(int nx, int wshift) {
@@ -544,7 +549,7 @@ inline hipError_t row_launch(const RowArgs<WT>& a, hipStream_t s) {
 template <int MODE, class WT>
 inline hipError_t row_configure(int nx) {
     return hipFuncSetAttribute((const void*)k_sno_row<MODE, WT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)row_lds(nx, row_wave_shift(nx)));
+                               (int)row_lds(nx, row_wave_shift(nx, 1LL << 40)));
 }
 
 }  // namespace
