@@ -86,10 +86,9 @@ __global__ void __launch_bounds__(1024) k_region_range(const uint8_t* __restrict
     range[blockIdx.x] = l | h << 8;
 }
 
-hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, int* count,
-                               hipStream_t s) {
-    *count = (int)((n + chunk - 1) / chunk);
-    hipLaunchKernelGGL(k_region_range, dim3(*count), dim3(1024), 0, s, region, n, chunk, range);
+hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, hipStream_t s) {
+    const unsigned count = (unsigned)((n + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_region_range, dim3(count), dim3(1024), 0, s, region, n, chunk, range);
     return hipGetLastError();
 }
 

@@ -858,7 +858,13 @@ int mm_create(mm_ctx** out, const mm_grid* g, const mm_params* p, const uint8_t*
         }
         c->scratch_bytes = (size_t)((char*)c->spec - (char*)c->kbuf) + (size_t)c->spec_elems * sizeof(cf);
     }
-    if (st == MM_OK && hipHostMalloc((void**)&c->hst, sizeof(DevState), hipHostMallocDefault) != hipSuccess)
+    // the pinned mirror of the solver state, and behind it the region ranges of
+    // the grid's chunks, which their kernel writes straight to it (a copy of them
+    // took 12 us of a small context's 94)
+    constexpr long long CHUNK = 1 << 15;
+    const size_t nch = (size_t)((c->ncell + CHUNK - 1) / CHUNK);
+    if (st == MM_OK &&
+        hipHostMalloc((void**)&c->hst, sizeof(DevState) + nch * sizeof(int), hipHostMallocDefault) != hipSuccess)
         st = MM_ENOMEM;
     if (st == MM_OK) st = map_err(static_scratch(c->device, &c->scratch));
     if (st == MM_OK) {
@@ -873,25 +879,15 @@ int mm_create(mm_ctx** out, const mm_grid* g, const mm_params* p, const uint8_t*
         if (e == hipSuccess)
             e = launch_set_state(c->st, 0.0, 1e-14, INFINITY, 1e-5, 0.8, 0.0, 0.0, 4, 1, 1, 0, c->stream);
         if (e == hipSuccess) e = launch_set_therm_step(c->st, 0, c->stream);
-        // whether the grid has a single region: ranges of chunks of cells (into
-        // the idle energy partials, four doubles per 256 cells and at least four)
-        int* range = reinterpret_cast<int*>(c->partials);
-        std::vector<int> hrange;
-        int nch = 0;
-        if (e == hipSuccess) e = launch_region_range(c->region, c->ncell, 1 << 15, range, &nch, c->stream);
-        try {
-            hrange.resize((size_t)nch);
-        } catch (...) {
-            e = hipErrorOutOfMemory;
-        }
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(hrange.data(), range, (size_t)nch * sizeof(int), hipMemcpyDeviceToHost, c->stream);
+        // whether the grid has a single region
+        int* range = reinterpret_cast<int*>(c->hst + 1);
+        if (e == hipSuccess) e = launch_region_range(c->region, c->ncell, CHUNK, range, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         st = map_err(e);
         if (st == MM_OK) {
-            c->ureg = hrange[0] & 255;
-            for (int r : hrange)
-                if (r != (c->ureg | c->ureg << 8)) {
+            c->ureg = range[0] & 255;
+            for (size_t i = 0; i < nch; ++i)
+                if (range[i] != (c->ureg | c->ureg << 8)) {
                     c->ureg = -1;
                     break;
                 }

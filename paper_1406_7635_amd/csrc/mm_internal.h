@@ -251,10 +251,9 @@ hipError_t launch_bset_state(DevState* st, int n, double t, double dt, double t_
 hipError_t launch_prepare_tables(const double* params64, RegionLut* lut, float* ptab,
                                  hipStream_t s);
 hipError_t launch_twiddles(cf* tw, int pt, hipStream_t s);
-// range[i] <- smallest | largest << 8 region of the i-th `chunk` of the n cells;
-// returns the number of chunks in *count
-hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, int* count,
-                               hipStream_t s);
+// range[i] <- smallest | largest << 8 region of the i-th `chunk` of the n cells
+// (range may be pinned host memory)
+hipError_t launch_region_range(const uint8_t* region, long long n, long long chunk, int* range, hipStream_t s);
 hipError_t launch_combine(const FieldArgs& a, hipStream_t s);
 // bd_in (optional): a magnetostatic field [3][ncell] to use instead of none
 hipError_t launch_local(const FieldArgs& a, hipStream_t s, int* nblocks_out, const float* bd_in = nullptr);
