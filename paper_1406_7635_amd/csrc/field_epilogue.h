@@ -386,7 +386,7 @@ __device__ inline unsigned int regions4(const uint8_t* region, unsigned int cell
 // half where more are needed.  No tableau's x pass combines more than four
 // derivatives, but the register count of a kernel is that of its largest case: with
 // 28 loads the fused pass of unpadded rows had 60 B of scratch a lane, or one
-// wave per SIMD less (1024 x 1024 periodic film, RK45 attempt 309 -> 346 us).
+// wave per SIMD less (1024 x 1024 periodic film, RK45 attempt 295 -> 346 us).
 template <int NK, int N>
 __device__ inline void stage_quads_nk(const FieldArgs& a, const Resolved& r, const unsigned int (&off)[N],
                                       f32x4 (&out)[N]) {
